@@ -177,6 +177,7 @@ struct wcl_lattice {
     int lps = 1;   // lanes per site of the full-lattice D-apply (tunable)
     uint64_t uid = 0;         // unique per lattice of the process (never reused)
     uint64_t clover_gen = 0;  // incremented whenever the clover field changes
+    int* link_flag = nullptr; // pinned: set by the device's SU(3) test of an upload
 };
 
 // device memory accounting against the context budget

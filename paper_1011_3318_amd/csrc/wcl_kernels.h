@@ -32,6 +32,8 @@ int launch_pack_spinor(const Geom& g, int prec, int nrhs, const double* aos, voi
                        hipStream_t st);
 int launch_unpack_spinor(const Geom& g, int prec, int nrhs, const void* soa, size_t stride, double* aos,
                          hipStream_t st);
+// *bad = 1 when some of the n links (AoS) is further than bound from SU(3)
+int launch_check_links(int64_t n, const double* aos, double bound, int* bad, hipStream_t st);
 int launch_pack_gauge(const Geom& g, const double* aos, void* g64, void* g32, void* g16, hipStream_t st);
 int launch_clover_build(const Geom& g, const void* g64, void* c64, void* c32, void* c16, hipStream_t st);
 int launch_pack_clover(const Geom& g, const double* host_dev, void* c64, void* c32, void* c16, hipStream_t st);
