@@ -3,7 +3,7 @@
 // chiral-basis spin projections and the per-site Wilson-clover stencil.
 #pragma once
 
-#include "wcl_internal.h"
+#include "wcl_kernels.h"
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f8v __attribute__((ext_vector_type(8)));
@@ -62,6 +62,12 @@ WCL_DEV void st_nt(V* p, V v) {
     *p = v;
 #endif
 }
+// NT = false: an ordinary store, for a line that a second store completes
+template <bool NT, typename V>
+WCL_DEV void stx(V* p, V v) {
+    if constexpr (NT) st_nt(p, v);
+    else *p = v;
+}
 
 // ------------------------------------------------------------ spinors ---
 // s[24]: component k = 3*spin + colour at s[2k] (re), s[2k+1] (im).
@@ -86,12 +92,13 @@ struct SpinorIO<WCL_F64> {
         load(base, V, i, s);
         return T(1);
     }
+    template <bool NT = true>
     WCL_DEV static void store(void* base, int V, int i, const T s[24]) {
         d2v* p = (d2v*)base;
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
             d2v v = {s[2 * k], s[2 * k + 1]};
-            st_nt(p + tix(k, i, 12), v);
+            stx<NT>(p + tix(k, i, 12), v);
         }
     }
 };
@@ -115,12 +122,13 @@ struct SpinorIO<WCL_F32> {
         load(base, V, i, s);
         return T(1);
     }
+    template <bool NT = true>
     WCL_DEV static void store(void* base, int V, int i, const T s[24]) {
         f4v* p = (f4v*)base;
 #pragma unroll
         for (int g = 0; g < 6; ++g) {
             f4v v = {s[4 * g], s[4 * g + 1], s[4 * g + 2], s[4 * g + 3]};
-            st_nt(p + tix(g, i, 6), v);
+            stx<NT>(p + tix(g, i, 6), v);
         }
     }
 };
@@ -829,6 +837,29 @@ WCL_DEV int xcd_remap(int b, int n) {
     int xcd = b % nx, k = b / nx;
     int q = n / nx, r = n % nx;
     return xcd < r ? xcd * (q + 1) + k : r * (q + 1) + (xcd - r) * q + k;
+}
+
+// Order in which a launch walks the 64-site tiles of a lattice field (or of
+// a half field, whose tiles hold the pairs of 128 sites).  Storage order runs
+// a column through all of t before the next one; when the cross-section is cut
+// in x or y too (extents such as 24: columns of 8 x 8 x 8), the x and y
+// neighbours outside the column are then a whole column away and every one of
+// them is fetched again after it left the L2.  The walk takes the columns of
+// one z range side by side instead: z range, t, (x, y) column, tile.
+// On 24^3x48 it fetches 1.12 instead of 1.37 GB per FP64 D-apply.
+//
+// tile of walk position w
+WCL_DEV int walk_tile(const TileWalk& k, int w) {
+    if (k.tiles == 0) return w;
+    const int q = w / k.tiles, u = q / k.nxy, z = u / k.Lt;
+    return ((z * k.nxy + (q - u * k.nxy)) * k.Lt + (u - z * k.Lt)) * k.tiles + (w - q * k.tiles);
+}
+
+// This lane's element of the walk: workgroup wg of 256 lanes takes walk
+// positions 4 wg .. 4 wg + 3, one tile per wavefront.
+WCL_DEV int walk_site(const TileWalk& k, int wg) {
+    const int w = __builtin_amdgcn_readfirstlane(wg * 4 + (int)(threadIdx.x >> 6));
+    return walk_tile(k, w) * 64 + (threadIdx.x & 63);
 }
 
 // --------------------------------------------------------- reductions ---

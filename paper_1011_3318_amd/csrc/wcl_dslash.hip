@@ -14,9 +14,14 @@
 #endif
 
 // A psi at site i, one 6x6 clover block at a time: acc = psi + c_sw kappa C psi.
-// NT: non-temporal loads of the links and clover (fields streamed once per
-// launch); cached loads when the launch's data fits the Infinity Cache or
-// several right-hand sides share the fields.
+// NT: non-temporal loads of the fields a launch reads once (the clover, and
+// in the exchange kernel the x and y links); cached loads when the launch's
+// data fits the Infinity Cache or several right-hand sides share the fields.
+// The links of hops whose neighbour is loaded are read twice, by the forward
+// hop of their site and the backward hop of the next one, and use cached loads
+// always: non-temporal ones cost 24^3x48 245 (FP64), 113 (FP32) and 44 us
+// (FP16) against 207, 92 and 43, and 32^4 296, 139 and 72 against 287, 131
+// and 65.
 template <bool NT, int GP, int SPI, typename T>
 WCL_DEV void clover_site(const DslashArgs& a, const char* in, int i, T acc[24]) {
     const int V = a.g.V;
@@ -47,7 +52,7 @@ WCL_DEV void hop_chain(const DslashArgs& a, const char* in, const int nbr[8], co
         hop_compute<K / 2, (K % 2) == 0>(sb[slot], ub[slot], mk * ph[K] * ss[slot], acc);
         if constexpr (K + D < 8) {
             ss[slot] = SpinorIO<SPI>::load_s(in, a.g.V, nbr[K + D], sb[slot]);
-            GaugeIO<GP>::template load_raw<NT>(a.gauge, a.g.V, (K + D) / 2, lnk[K + D], ub[slot]);
+            GaugeIO<GP>::template load_raw<false>(a.gauge, a.g.V, (K + D) / 2, lnk[K + D], ub[slot]);
         }
         hop_chain<K + 1, D, NT, GP, SPI>(a, in, nbr, lnk, ph, mk, sb, ss, ub, acc);
     }
@@ -67,7 +72,7 @@ WCL_DEV void dslash_site(const DslashArgs& a, const char* in, int i, T acc[24]) 
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         ss[k] = SpinorIO<SPI>::load_s(in, a.g.V, nbr[k], sb[k]);
-        GaugeIO<GP>::template load_raw<NT>(a.gauge, a.g.V, k / 2, lnk[k], ub[k]);
+        GaugeIO<GP>::template load_raw<false>(a.gauge, a.g.V, k / 2, lnk[k], ub[k]);
     }
     clover_site<NT, GP, SPI>(a, in, i, acc);
     hop_chain<0, D, NT, GP, SPI>(a, in, nbr, lnk, ph, T(-a.kappa), sb, ss, ub, acc);
@@ -85,7 +90,7 @@ WCL_DEV void hop_chain16(const DslashArgs& a, const char* in, const int nbr[8], 
         hop_compute16<K / 2, (K % 2) == 0>(sb[slot], ub[slot], mk * ph[K] * ss[slot], z, acc);
         if constexpr (K + D < 8) {
             ss[slot] = load_spinor16(in, a.g.V, nbr[K + D], sb[slot]);
-            load_link16<NT>(a.gauge, a.g.V, (K + D) / 2, lnk[K + D], z, ub[slot]);
+            load_link16<false>(a.gauge, a.g.V, (K + D) / 2, lnk[K + D], z, ub[slot]);
         }
         hop_chain16<K + 1, D, NT>(a, in, nbr, lnk, ph, mk, z, sb, ss, ub, acc);
     }
@@ -105,7 +110,7 @@ WCL_DEV void dslash_site16(const DslashArgs& a, const char* in, int i, float acc
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         ss[k] = load_spinor16(in, a.g.V, nbr[k], sb[k]);
-        load_link16<NT>(a.gauge, a.g.V, k / 2, lnk[k], z, ub[k]);
+        load_link16<false>(a.gauge, a.g.V, k / 2, lnk[k], z, ub[k]);
     }
     h2v x16[12];
     const float sc = load_spinor16(in, a.g.V, i, x16);
@@ -123,7 +128,7 @@ __global__ __launch_bounds__(256, WCL_DSLASH_MINWAVES) void k_dslash(DslashArgs 
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
     const int rhs = lb % a.nrhs;
     if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
-    const int i = (lb / a.nrhs) * 256 + threadIdx.x;
+    const int i = walk_site(a.walk, lb / a.nrhs);
     const bool active = i < a.g.V;
     T acc[24];
     if (active) {
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy(DslashArgs a
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         ss[(4 + k) % D] = SpinorIO<SPI>::load_s(in, V, nbr[4 + k], sb[(4 + k) % D]);
-        GaugeIO<GP>::template load_raw<NT>(a.gauge, V, (4 + k) / 2, lnk[4 + k], ub[(4 + k) % D]);
+        GaugeIO<GP>::template load_raw<false>(a.gauge, V, (4 + k) / 2, lnk[4 + k], ub[(4 + k) % D]);
     }
 
     hop_chain<4, D, NT, GP, SPI>(a, in, nbr, lnk, ph, mk, sb, ss, ub, acc);
@@ -460,7 +465,7 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy16(DslashArgs
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         ss[(4 + k) % D] = load_spinor16(in, V, nbr[4 + k], sb[(4 + k) % D]);
-        load_link16<NT>(a.gauge, V, (4 + k) / 2, lnk[4 + k], z, ub[(4 + k) % D]);
+        load_link16<false>(a.gauge, V, (4 + k) / 2, lnk[4 + k], z, ub[(4 + k) % D]);
     }
     hop_chain16<4, D, NT>(a, in, nbr, lnk, ph, mk, z, sb, ss, ub, acc);
 
@@ -624,7 +629,9 @@ static size_t dslash_launch_bytes(int V, int gp, int spi, int spo) {
 }
 
 template <int GP, int SPI, int SPO, int EPI, int SPY>
-static int launch_t(const DslashArgs& a, hipStream_t st) {
+static int launch_t(const DslashArgs& a0, hipStream_t st) {
+    DslashArgs a = a0;
+    a.walk = tile_walk(a.g, 1);
     const int tiles = dslash_partials_per_rhs(a.g.V, a.lps);
     switch (a.lps) {
         case 2: k_dslash_ml<GP, SPI, SPO, EPI, SPY, 2><<<tiles * a.nrhs, 256, 0, st>>>(a); break;

@@ -12,8 +12,22 @@ struct Scal {
     int active, breakdown;
 };
 
+// order of the tiles in a launch, see walk_tile in wcl_device.h
+struct TileWalk {
+    int tiles;   // 64-site tiles of one column at one t; 0: storage order
+    int nxy;     // columns of one z range
+    int Lt;
+};
+// sites: sites per tile element (1: lattice fields, 2: half fields)
+inline TileWalk tile_walk(const Geom& g, int sites) {
+    const int nxy = g.nC[0] * g.nC[1];
+    if (nxy == 1 || g.S % (64 * sites) != 0) return TileWalk{0, 1, 1};
+    return TileWalk{g.S / (64 * sites), nxy, g.L[3]};
+}
+
 struct DslashArgs {
     Geom g;
+    TileWalk walk;       // set by launch_dslash
     const void* gauge;
     const void* clover;
     const void* in;

@@ -1,0 +1,43 @@
+"""D-applies that walk the lattice's tiles in another order than they are
+stored (columns cut in x or y) against the oracle."""
+import numpy as np
+import pytest
+
+from helpers import rel_err
+from oracle import Oracle
+from paper_1011_3318_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# column cross-section and the 64-site tiles of one column at one t:
+#   24x8x8x4    8x8x8, 8 tiles (4 of a half field), three columns in x
+#   12x12x4x6   4x4x4, 1 tile; half fields: storage order
+#   12x20x16x4  4x4x8, 2 tiles (1 of a half field), two z ranges of 15 columns
+#   10x6x4x6    2x2x4: storage order throughout
+DIMS = [(24, 8, 8, 4), (12, 12, 4, 6), (12, 20, 16, 4), (10, 6, 4, 6)]
+BC = (1, 1, 1, -1)
+
+
+@pytest.fixture(scope="module")
+def W():
+    from paper_1011_3318_amd import wcl
+    return wcl
+
+
+# the tolerances of the D-apply's and the Schur operator's own tests
+@pytest.mark.parametrize("dims", DIMS)
+def test_walk_matches_oracle(W, dims):
+    ctx = W.Context(0)
+    U = I.random_gauge(dims, 0.5, 1)
+    lat = W.Lattice(ctx, dims, BC)
+    lat.upload_gauge(U)
+    o = Oracle(dims, U, bc=BC)
+    psi = I.gaussian_source(dims, 4, nrhs=2)
+    kappa, csw = 0.126, 1.3
+    ref = [o.apply_D(psi[k], kappa, csw) for k in range(2)]
+    for prec, tol in ((W.F64, 1e-13), (W.F32, 1e-5), (W.F16, 2e-3)):
+        out = lat.empty(prec, 2)
+        got = lat.unpack(lat.apply_D(prec, kappa, csw, lat.pack(psi, prec, 2), out, nrhs=2), prec, 2)
+        assert max(rel_err(got[k], ref[k]) for k in range(2)) <= tol
+    lat.close()
+    ctx.close()
