@@ -44,6 +44,11 @@ int wcl_dev_alloc(wcl_ctx* ctx, void** p, size_t bytes) {
     return WCL_OK;
 }
 
+uint64_t wcl_dev_room(wcl_ctx* ctx) {
+    std::lock_guard<std::mutex> g(ctx->mu);
+    return ctx->budget > ctx->in_use ? ctx->budget - ctx->in_use : 0;
+}
+
 void wcl_dev_free(wcl_ctx* ctx, void* p, size_t bytes) {
     if (!p) return;
     (void)hipFree(p);
@@ -233,7 +238,8 @@ int wcl_upload_gauge(wcl_lattice* lat, const double* U) {
         return WCL_EINVAL;
     }
     // The links are copied first and tested on the device: on one host thread
-    // the test of a 16^3x32 field takes 33 ms, the copy of it 3 ms.  Nothing of the lattice changes before the field has passed.
+    // the test of a 16^3x32 field takes 33 ms, the copy of it 3 ms.  Nothing of
+    // the lattice changes before the field has passed.
     const int64_t n = lat->V * 4;
     const size_t bytes = (size_t)n * 18 * sizeof(double);
     WCL_CHECK(set_device(lat->ctx));

@@ -846,7 +846,8 @@ WCL_DEV int xcd_remap(int b, int n) {
 // neighbours outside the column are then a whole column away and every one of
 // them is fetched again after it left the L2.  The walk takes the columns of
 // one z range side by side instead: z range, t, (x, y) column, tile.
-// On 24^3x48 it fetches 1.12 instead of 1.37 GB per FP64 D-apply.
+// On 24^3x48 it fetches 1.12 instead of 1.37 GB per FP64 D-apply, 450 + 360
+// instead of 520 + 427 MB per FP32 Dhat.
 //
 // tile of walk position w
 WCL_DEV int walk_tile(const TileWalk& k, int w) {

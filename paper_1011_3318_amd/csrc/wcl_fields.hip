@@ -376,26 +376,34 @@ int launch_unpack_clover(const Geom& g, const void* c64, double* host_dev, hipSt
 // elimination with partial pivoting (A need not be positive definite); the
 // inverse is Hermitian and is stored packed exactly like the clover field
 // (upper triangle), so the clover loaders and herm6_apply serve it too.
+// In place, every index a compile-time constant (rows and columns are
+// exchanged by compare and select), so that the block stays in registers.
 __device__ bool herm6_inverse(const double c[36], double ck, double out[36]) {
-    double m[6][6][2], v[6][6][2];
-    for (int a = 0; a < 6; ++a)
-        for (int b = 0; b < 6; ++b) {
-            m[a][b][0] = m[a][b][1] = 0.0;
-            v[a][b][0] = a == b ? 1.0 : 0.0;
-            v[a][b][1] = 0.0;
-        }
-    for (int a = 0; a < 6; ++a) m[a][a][0] = 1.0 + ck * c[a];
-    int k = 0;
-    for (int a = 0; a < 6; ++a)
-        for (int b = a + 1; b < 6; ++b, ++k) {
-            m[a][b][0] = ck * c[6 + 2 * k];
-            m[a][b][1] = ck * c[6 + 2 * k + 1];
-            m[b][a][0] = m[a][b][0];
-            m[b][a][1] = -m[a][b][1];
-        }
+    double m[6][6][2];
+    int pr[6];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        m[a][a][0] = 1.0 + ck * c[a];
+        m[a][a][1] = 0.0;
+    }
+    {
+        int k = 0;
+#pragma unroll
+        for (int a = 0; a < 6; ++a)
+#pragma unroll
+            for (int b = a + 1; b < 6; ++b, ++k) {
+                m[a][b][0] = ck * c[6 + 2 * k];
+                m[a][b][1] = ck * c[6 + 2 * k + 1];
+                m[b][a][0] = m[a][b][0];
+                m[b][a][1] = -m[a][b][1];
+            }
+    }
+    bool ok = true;
+#pragma unroll
     for (int col = 0; col < 6; ++col) {
         int piv = col;
         double best = m[col][col][0] * m[col][col][0] + m[col][col][1] * m[col][col][1];
+#pragma unroll
         for (int r = col + 1; r < 6; ++r) {
             const double q = m[r][col][0] * m[r][col][0] + m[r][col][1] * m[r][col][1];
             if (q > best) {
@@ -403,47 +411,67 @@ __device__ bool herm6_inverse(const double c[36], double ck, double out[36]) {
                 piv = r;
             }
         }
-        if (!(best > 0.0) || !isfinite(best)) return false;
-        if (piv != col)
-            for (int j = 0; j < 6; ++j)
-                for (int z = 0; z < 2; ++z) {
-                    double t = m[col][j][z];
-                    m[col][j][z] = m[piv][j][z];
-                    m[piv][j][z] = t;
-                    t = v[col][j][z];
-                    v[col][j][z] = v[piv][j][z];
-                    v[piv][j][z] = t;
-                }
-        // row col /= pivot
-        const double pr = m[col][col][0] / best, pi = -m[col][col][1] / best;   // 1 / pivot
+        ok = ok && best > 0.0 && isfinite(best);
+        pr[col] = piv;
+#pragma unroll
+        for (int r = col + 1; r < 6; ++r)
+            if (piv == r) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j)
+#pragma unroll
+                    for (int z = 0; z < 2; ++z) {
+                        const double t = m[col][j][z];
+                        m[col][j][z] = m[r][j][z];
+                        m[r][j][z] = t;
+                    }
+            }
+        const double ir = m[col][col][0] / best, ii = -m[col][col][1] / best;   // 1 / pivot
+        m[col][col][0] = 1.0;
+        m[col][col][1] = 0.0;
+#pragma unroll
         for (int j = 0; j < 6; ++j) {
-            double re = m[col][j][0] * pr - m[col][j][1] * pi, im = m[col][j][0] * pi + m[col][j][1] * pr;
+            const double re = m[col][j][0] * ir - m[col][j][1] * ii, im = m[col][j][0] * ii + m[col][j][1] * ir;
             m[col][j][0] = re;
             m[col][j][1] = im;
-            re = v[col][j][0] * pr - v[col][j][1] * pi;
-            im = v[col][j][0] * pi + v[col][j][1] * pr;
-            v[col][j][0] = re;
-            v[col][j][1] = im;
         }
+#pragma unroll
         for (int r = 0; r < 6; ++r) {
             if (r == col) continue;
             const double fr = m[r][col][0], fi = m[r][col][1];
+            m[r][col][0] = m[r][col][1] = 0.0;
+#pragma unroll
             for (int j = 0; j < 6; ++j) {
                 m[r][j][0] -= fr * m[col][j][0] - fi * m[col][j][1];
                 m[r][j][1] -= fr * m[col][j][1] + fi * m[col][j][0];
-                v[r][j][0] -= fr * v[col][j][0] - fi * v[col][j][1];
-                v[r][j][1] -= fr * v[col][j][1] + fi * v[col][j][0];
             }
         }
     }
-    for (int a = 0; a < 6; ++a) out[a] = v[a][a][0];
-    k = 0;
+    // (P A)^{-1} P: the row exchanges undone as column exchanges, last first
+#pragma unroll
+    for (int col = 5; col >= 0; --col)
+#pragma unroll
+        for (int r = col + 1; r < 6; ++r)
+            if (pr[col] == r) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j)
+#pragma unroll
+                    for (int z = 0; z < 2; ++z) {
+                        const double t = m[j][col][z];
+                        m[j][col][z] = m[j][r][z];
+                        m[j][r][z] = t;
+                    }
+            }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) out[a] = m[a][a][0];
+    int k = 0;
+#pragma unroll
     for (int a = 0; a < 6; ++a)
+#pragma unroll
         for (int b = a + 1; b < 6; ++b, ++k) {
-            out[6 + 2 * k] = v[a][b][0];
-            out[6 + 2 * k + 1] = v[a][b][1];
+            out[6 + 2 * k] = m[a][b][0];
+            out[6 + 2 * k + 1] = m[a][b][1];
         }
-    return true;
+    return ok;
 }
 
 __global__ __launch_bounds__(64) void k_site_inverse(Geom g, const void* c64, double ck, void* a64, void* a32, void* a16,
@@ -463,6 +491,61 @@ __global__ __launch_bounds__(64) void k_site_inverse(Geom g, const void* c64, do
 int launch_site_inverse(const Geom& g, const void* c64, double kappa, double csw, void* a64, void* a32, void* a16,
                         int* bad, hipStream_t st) {
     k_site_inverse<<<(g.V + 63) / 64, 64, 0, st>>>(g, c64, csw * kappa, a64, a32, a16, bad);
+    WCL_HIP(hipGetLastError());
+    return WCL_OK;
+}
+
+// ---------------------------------------------------- even-odd fields ---
+// Parity-split copies for the even-odd reduction (half index h = site / 2):
+// one thread per (site, clover block).  Every site's block is inverted, so
+// that a singular one is found at either parity; the odd sites' inverses are
+// kept.  Bound by the FP64 elimination (registers: one 6x6 block per thread).
+template <int P>
+__global__ __launch_bounds__(128) void k_eo_fields(Geom g, const void* c64, const void* clover, const void* gauge,
+                                                  double ck, void* ainv, void* clov, void* links, size_t links_stride,
+                                                  int* bad) {
+    using T = typename Real<P>::T;
+    constexpr int W = 16 / sizeof(T);              // reals per 16-byte element
+    using E = T __attribute__((ext_vector_type(W)));
+    const int b = threadIdx.x >> 6;                // clover block: uniform over a wavefront
+    const int i = blockIdx.x * 64 + (threadIdx.x & 63);
+    if (i >= g.V) return;
+    int x[4];
+    geom_coords(g, i, x);
+    const int p = (x[0] + x[1] + x[2] + x[3]) & 1, h = i >> 1;
+    double c[36], r[36];
+    CloverBlk<WCL_F64>::template load<false>(c64, g.V, i, b, c);
+    if (!herm6_inverse(c, ck, r)) atomicOr(bad, 1);
+    constexpr int NB = 36 / W, NC = 2 * NB, NG = 48 / W;
+    if (p) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            E e;
+#pragma unroll
+            for (int j = 0; j < W; ++j) e[j] = (T)r[W * k + j];
+            ((E*)ainv)[tix(NB * b + k, h, NC)] = e;
+        }
+    } else {
+        for (int k = 0; k < NB; ++k) ((E*)clov)[tix(NB * b + k, h, NC)] = ((const E*)clover)[tix(NB * b + k, i, NC)];
+    }
+    if (links) {
+        E* l = (E*)((char*)links + p * links_stride);
+        for (int k = 0; k < NG / 2; ++k) {
+            const int n = NG / 2 * b + k;
+            l[tix(n, h, NG)] = ((const E*)gauge)[tix(n, i, NG)];
+        }
+    }
+}
+
+int launch_eo_fields(const Geom& g, int prec, const void* c64, const void* clover, const void* gauge, double kappa,
+                     double csw, void* ainv, void* clov, void* links, size_t links_stride, int* bad, hipStream_t st) {
+    const int grid = (g.V + 63) / 64;
+    if (prec == WCL_F64)
+        k_eo_fields<WCL_F64><<<grid, 128, 0, st>>>(g, c64, clover, gauge, csw * kappa, ainv, clov, links, links_stride,
+                                                   bad);
+    else
+        k_eo_fields<WCL_F32><<<grid, 128, 0, st>>>(g, c64, clover, gauge, csw * kappa, ainv, clov, links, links_stride,
+                                                   bad);
     WCL_HIP(hipGetLastError());
     return WCL_OK;
 }

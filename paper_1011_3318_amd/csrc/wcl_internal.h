@@ -182,6 +182,7 @@ struct wcl_lattice {
 
 // device memory accounting against the context budget
 int wcl_dev_alloc(wcl_ctx* ctx, void** p, size_t bytes);
+uint64_t wcl_dev_room(wcl_ctx* ctx);   // what the budget still allows
 void wcl_dev_free(wcl_ctx* ctx, void* p, size_t bytes);
 
 int check_prec(int prec);

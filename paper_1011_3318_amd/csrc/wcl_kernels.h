@@ -59,20 +59,23 @@ int launch_dslash(const DslashArgs& a, int gp, int spi, int spo, int epi, int sp
 // --------------------------------------------------------- even-odd ----
 // Steps of the even-odd reduction (wcl_evenodd.hip); "half" fields hold the
 // V/2 sites of one parity, the site of parity p in pair (2h, 2h+1) at index h.
-enum { EO_INV = 0, EO_SCHUR = 1, EO_PREP = 2, EO_RECON = 3, EO_SITEINV = 4, EO_EXTRACT = 5, EO_INSERT = 6,
-       EO_ZERO = 7 };
+enum { EO_INV = 0, EO_SCHUR = 1, EO_PREP = 2, EO_RECON = 3, EO_SITEINV = 4 };
 struct EoArgs {
     Geom g;
+    TileWalk walk;       // set by launch_eo
     int Vh;              // V / 2
     int parity;          // parity of the sites the launch computes
-    const void* gauge;   // full-lattice fields, precision of the launch
-    const void* clover;
-    const void* ainv;    // site-term inverse, clover layout
-    const void* in;      // half field of the other parity (hop source)
-    const void* in2;     // half field of `parity` (EO_SCHUR site-term operand, EO_INSERT source)
-    const void* y;       // full field (EO_PREP/RECON/SITEINV/EXTRACT) or half field (EO_SCHUR axpy)
+    int full;            // EO_INV, EO_SCHUR: psi_e and Dhat psi_e are full-lattice fields
+    const void* gauge;   // full-lattice links, precision of the launch
+    const void* links;   // optional: parity-split links (even half field, then odd), used instead
+    size_t links_stride; // bytes of one of them
+    const void* clover;  // clover of the even sites, half field
+    const void* ainv;    // site-term inverse of the odd sites, half field, clover layout
+    const void* in;      // half field of the other parity (hop source; EO_INV with full: full field)
+    const void* in2;     // half field of `parity` (EO_SCHUR site-term operand; with full: full field)
+    const void* y;       // full field (EO_PREP/RECON/SITEINV) or half field (EO_SCHUR axpy)
     const void* a;       // half field: left vector of the DS_DOT partials
-    void* out;           // half field, or full field for EO_RECON/INSERT/ZERO
+    void* out;           // half field, or full field (EO_RECON; EO_SCHUR with full)
     size_t in_stride, in2_stride, y_stride, a_stride, out_stride;   // bytes per rhs
     double kappa, csw;
     int nrhs;
@@ -186,6 +189,12 @@ int launch_blk_gather(const BlockArgs& a, int vj_prec, hipStream_t st);
 // FP64, FP32 and FP16; *bad (device int) is set when some A(x) is singular
 int launch_site_inverse(const Geom& g, const void* c64, double kappa, double csw, void* a64, void* a32, void* a16,
                         int* bad, hipStream_t st);
+// Fields of the even-odd reduction at precision prec (FP64 or FP32), as half
+// fields: ainv = A^{-1} of the odd sites, clov = C of the even sites, links
+// (optional) = the links of the even sites, then of the odd ones, links_stride
+// bytes apart.  *bad is set when A is singular at some site of either parity.
+int launch_eo_fields(const Geom& g, int prec, const void* c64, const void* clover, const void* gauge, double kappa,
+                     double csw, void* ainv, void* clov, void* links, size_t links_stride, int* bad, hipStream_t st);
 int launch_blk_unpack(const BlockArgs& a, const float* ws, double* out, hipStream_t st);
 // ------------------------------------------------------------- solvers --
 struct Workspace;

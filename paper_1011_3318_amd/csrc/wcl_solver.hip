@@ -78,6 +78,13 @@ struct Workspace {
     uint64_t ainv_uid = 0, ainv_gen = 0;
     double ainv_kappa = 0.0, ainv_csw = 0.0;
     const void* ainv_ptr = nullptr;
+    // keys of the even-odd fields held in "eo.ainv.*", "eo.clov.*" and
+    // "eo.links.*", one per precision (see eo_fields)
+    struct EoKey {
+        uint64_t uid = 0, gen = 0;
+        double kappa = 0.0, csw = 0.0;
+        const void *ainv = nullptr, *clov = nullptr, *links = nullptr;
+    } eo_key[2];
     struct Item {
         std::string name;
         void* p;
@@ -112,6 +119,11 @@ struct Workspace {
         items.push_back(it);
         *out = it.p;
         return WCL_OK;
+    }
+    bool has(const std::string& name, size_t bytes) const {
+        for (const auto& it : items)
+            if (it.name == name) return it.bytes >= bytes;
+        return false;
     }
     int host_scal(const std::string& name, size_t n, Scal** out) {
         for (auto& pp : pinned)
@@ -380,6 +392,49 @@ static int site_inverse(wcl_lattice* lat, Workspace* ws, double kappa, double cs
     return WCL_OK;
 }
 
+// The fields of the even-odd reduction at precision prec (see
+// launch_eo_fields), built for (lattice, clover field, kappa, csw) and kept in
+// the workspace until one of them changes.  The parity-split links are an
+// extra copy, made only while the budget leaves room for the vectors of a
+// solve beside it; else the full-lattice links serve.
+struct EoFields {
+    void *ainv = nullptr, *clov = nullptr, *links = nullptr;
+};
+static int eo_fields(wcl_lattice* lat, Workspace* ws, double kappa, double csw, int prec, bool want_links,
+                     hipStream_t st, EoFields* f) {
+    const int64_t Vh = lat->V / 2;
+    const std::string tag = prec == WCL_F64 ? ".f64" : ".f32";
+    WCL_CHECK(ws->get("eo.ainv" + tag, clover_bytes(prec, Vh), &f->ainv));
+    WCL_CHECK(ws->get("eo.clov" + tag, clover_bytes(prec, Vh), &f->clov));
+    int* bad = nullptr;
+    WCL_CHECK(ws->get("ainv.bad", 256, (void**)&bad));
+    if (want_links) {
+        const size_t bytes = 2 * gauge_bytes(prec, Vh), room = 16 * spinor_rhs_bytes(WCL_F64, lat->V);
+        if (ws->has("eo.links" + tag, bytes) || wcl_dev_room(lat->ctx) >= bytes + room) {
+            const int rc = ws->get("eo.links" + tag, bytes, &f->links);
+            if (rc == WCL_ENOMEM) f->links = nullptr;
+            else WCL_CHECK(rc);
+        }
+    }
+    Workspace::EoKey& k = ws->eo_key[prec == WCL_F64 ? 0 : 1];
+    if (k.uid == lat->uid && k.gen == lat->clover_gen && k.kappa == kappa && k.csw == csw && k.ainv == f->ainv &&
+        k.clov == f->clov && (!f->links || k.links == f->links))
+        return WCL_OK;
+    k = Workspace::EoKey{};
+    int hbad = 0;
+    WCL_HIP(hipMemcpyAsync(bad, &hbad, sizeof(int), hipMemcpyHostToDevice, st));
+    WCL_CHECK(launch_eo_fields(lat->g, prec, lat->clover[WCL_F64], lat->clover[prec], lat->gauge[prec], kappa, csw,
+                               f->ainv, f->clov, f->links, gauge_bytes(prec, Vh), bad, st));
+    WCL_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
+    WCL_HIP(hipStreamSynchronize(st));
+    if (hbad) {
+        wcl_set_error("the site term 1 + c_sw kappa C(x) is singular at some site (kappa %g, c_sw %g)", kappa, csw);
+        return WCL_EINVAL;
+    }
+    k = Workspace::EoKey{lat->uid, lat->clover_gen, kappa, csw, f->ainv, f->clov, f->links};
+    return WCL_OK;
+}
+
 static void tl_mark(Timeline* tl, int cat) {
     if (tl) tl->mark(cat);
 }
@@ -637,9 +692,9 @@ struct Engine {
     Scal* hmap;   // h as the device addresses it (written by the finalize kernels)
     hipEvent_t ev = nullptr;   // recorded after each iteration's last finalize
     // even-odd: the operator is the Schur complement Dhat on the even half
-    // fields (vectors of V/2 sites); eo_ainv = site-term inverse at precision P
+    // fields (vectors of V/2 sites); eo_f = the reduction's fields at precision P
     int eo = 0;
-    const void* eo_ainv = nullptr;
+    EoFields eo_f;
     void* eo_t = nullptr;   // half-field temporary A_oo^{-1} H_oe x
     // |r| / |b| of each rhs at the start of the current iteration (what the
     // preconditioner's accuracy is measured against; 1 before the first)
@@ -682,8 +737,10 @@ struct Engine {
         e.g = lat->g;
         e.Vh = (int)V;
         e.gauge = lat->gauge[gp];
-        e.clover = lat->clover[gp];
-        e.ainv = eo_ainv;
+        e.links = eo_f.links;
+        e.links_stride = gauge_bytes(gp, V);
+        e.clover = eo_f.clov;
+        e.ainv = eo_f.ainv;
         e.in_stride = e.in2_stride = e.y_stride = e.a_stride = e.out_stride = spinor_rhs_bytes(P, V);
         e.kappa = kappa;
         e.csw = csw;
@@ -1020,13 +1077,15 @@ static int host_norms2(Workspace* ws, int prec, int64_t V, int nrhs, const void*
     return WCL_OK;
 }
 
-static EoArgs eo_args(const wcl_lattice* lat, int prec, const void* ainv, double kappa, double csw, int nrhs) {
+static EoArgs eo_args(const wcl_lattice* lat, int prec, const EoFields& f, double kappa, double csw, int nrhs) {
     EoArgs e{};
     e.g = lat->g;
     e.Vh = (int)(lat->V / 2);
     e.gauge = lat->gauge[prec];
-    e.clover = lat->clover[prec];
-    e.ainv = ainv;
+    e.links = f.links;
+    e.links_stride = gauge_bytes(prec, e.Vh);
+    e.clover = f.clov;
+    e.ainv = f.ainv;
     e.in_stride = e.in2_stride = e.a_stride = spinor_rhs_bytes(prec, e.Vh);
     e.y_stride = e.out_stride = spinor_rhs_bytes(prec, lat->V);
     e.kappa = kappa;
@@ -1087,17 +1146,17 @@ int nested_solve(wcl_lattice* lat, Workspace* ws, const wcl_solver_params* prm, 
     std::vector<double> tol_rhs(nrhs, tol);
     std::vector<double> eta2;
     if (eo) {
-        void* inv[3];
-        WCL_CHECK(site_inverse(lat, ws, kappa, csw, st, inv));
+        // the FP64 level applies Dhat a few times per solve: its links are not
+        // copied
         inner.eo = outer.eo = 1;
-        inner.eo_ainv = inv[WCL_F32];
-        outer.eo_ainv = inv[WCL_F64];
+        WCL_CHECK(eo_fields(lat, ws, kappa, csw, WCL_F64, false, st, &outer.eo_f));
+        WCL_CHECK(eo_fields(lat, ws, kappa, csw, WCL_F32, true, st, &inner.eo_f));
         const size_t h64 = spinor_rhs_bytes(WCL_F64, Vs) * nrhs;
-        void *be = nullptr, *te = nullptr, *xe = nullptr;
+        void *be = nullptr, *xe = nullptr;
         WCL_CHECK(ws->get("eo.b", h64, &be));
-        WCL_CHECK(ws->get("eo.t", h64, &te));
         WCL_CHECK(ws->get("eo.x", h64, &xe));
-        EoArgs e = eo_args(lat, WCL_F64, inv[WCL_F64], kappa, csw, nrhs);
+        void* te = xe;   // A_oo^{-1} eta_o, done with before x_e is started
+        EoArgs e = eo_args(lat, WCL_F64, outer.eo_f, kappa, csw, nrhs);
         ws->tl.mark(CAT_DSLASH);
         e.parity = 1;   // te = A_oo^{-1} eta_o
         e.y = eta;
@@ -1159,18 +1218,13 @@ int nested_solve(wcl_lattice* lat, Workspace* ws, const wcl_solver_params* prm, 
     if (rc == WCL_OK && eo) {
         // phi_o = A_oo^{-1} (eta_o - H_oe x_e), phi_e = x_e; then the full
         // system's true residual
-        void* inv[3];
-        WCL_CHECK(site_inverse(lat, ws, kappa, csw, st, inv));
-        EoArgs e = eo_args(lat, WCL_F64, inv[WCL_F64], kappa, csw, nrhs);
+        EoArgs e = eo_args(lat, WCL_F64, outer.eo_f, kappa, csw, nrhs);
         ws->tl.mark(CAT_DSLASH);
         e.parity = 1;
         e.in = sol_vec;
         e.y = eta;
         e.out = phi;
         WCL_CHECK(launch_eo(e, WCL_F64, EO_RECON, DS_PLAIN, st));
-        e.parity = 0;
-        e.in2 = sol_vec;
-        WCL_CHECK(launch_eo(e, WCL_F64, EO_INSERT, DS_PLAIN, st));
         void* rfull = nullptr;
         WCL_CHECK(ws->get("eo.res", spinor_rhs_bytes(WCL_F64, lat->V) * nrhs, &rfull));
         DslashArgs d{};
@@ -1350,38 +1404,28 @@ int wcl_apply_schur(wcl_lattice* lat, int prec, double kappa, double csw, const 
     WCL_HIP(hipSetDevice(lat->ctx->device));
     hipStream_t st = (hipStream_t)stream;
     Workspace* ws = lattice_ws(lat);
-    void* inv[3];
-    WCL_CHECK(site_inverse(lat, ws, kappa, csw, st, inv));
     const int64_t Vh = lat->V / 2;
-    const size_t hb = spinor_rhs_bytes(prec, Vh) * nrhs;
-    void *xe = nullptr, *to = nullptr, *ye = nullptr;
-    WCL_CHECK(ws->get("schur.x", hb, &xe));
-    WCL_CHECK(ws->get("schur.t", hb, &to));
-    WCL_CHECK(ws->get("schur.y", hb, &ye));
-    EoArgs e = eo_args(lat, prec, inv[prec], kappa, csw, nrhs);
     const size_t hs = spinor_rhs_bytes(prec, Vh), fs = spinor_rhs_bytes(prec, lat->V);
-    e.parity = 0;   // x_e = in on the even sites
-    e.y = in_dev;
-    e.out = xe;
-    e.out_stride = hs;
-    WCL_CHECK(launch_eo(e, prec, EO_EXTRACT, DS_PLAIN, st));
-    e.parity = 1;   // t_o = A_oo^{-1} H_oe x_e
-    e.in = xe;
+    void* to = nullptr;
+    WCL_CHECK(ws->get("schur.t", hs * nrhs, &to));
+    EoFields f;
+    WCL_CHECK(eo_fields(lat, ws, kappa, csw, prec, true, st, &f));
+    EoArgs e = eo_args(lat, prec, f, kappa, csw, nrhs);
+    e.full = 1;
+    e.parity = 1;   // t_o = A_oo^{-1} H_oe x_e, x_e = in on the even sites
+    e.in = in_dev;
+    e.in_stride = fs;
     e.out = to;
+    e.out_stride = hs;
     WCL_CHECK(launch_eo(e, prec, EO_INV, DS_PLAIN, st));
-    e.parity = 0;   // y_e = A_ee x_e - H_eo t_o
+    e.parity = 0;   // out_e = A_ee x_e - H_eo t_o, out_o = 0
     e.in = to;
-    e.in2 = xe;
-    e.out = ye;
-    WCL_CHECK(launch_eo(e, prec, EO_SCHUR, DS_PLAIN, st));
+    e.in_stride = hs;
+    e.in2 = in_dev;
+    e.in2_stride = fs;
     e.out = out_dev;
     e.out_stride = fs;
-    e.parity = 1;
-    WCL_CHECK(launch_eo(e, prec, EO_ZERO, DS_PLAIN, st));
-    e.parity = 0;
-    e.in2 = ye;
-    WCL_CHECK(launch_eo(e, prec, EO_INSERT, DS_PLAIN, st));
-    return WCL_OK;
+    return launch_eo(e, prec, EO_SCHUR, DS_PLAIN, st);
 }
 
 int wcl_solve_nested_bicgstab(wcl_lattice* lat, const wcl_solver_params* p, double kappa, double csw,

@@ -1,5 +1,6 @@
-"""D-applies that walk the lattice's tiles in another order than they are
-stored (columns cut in x or y) against the oracle."""
+"""Launches that walk the lattice's tiles in another order than they are
+stored (columns cut in x or y), and the parity-split fields of the even-odd
+operator with and without room for the split links, against the oracle."""
 import numpy as np
 import pytest
 
@@ -39,5 +40,33 @@ def test_walk_matches_oracle(W, dims):
         out = lat.empty(prec, 2)
         got = lat.unpack(lat.apply_D(prec, kappa, csw, lat.pack(psi, prec, 2), out, nrhs=2), prec, 2)
         assert max(rel_err(got[k], ref[k]) for k in range(2)) <= tol
+    for prec, tol in ((W.F64, 1e-13), (W.F32, 1e-5)):
+        out = lat.empty(prec, 2)
+        got = lat.unpack(lat.apply_schur(prec, kappa, csw, lat.pack(psi, prec, 2), out, nrhs=2), prec, 2)
+        assert max(rel_err(got[k], o.apply_schur(psi[k], kappa, csw)) for k in range(2)) <= tol
     lat.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("dims", DIMS[:2])
+def test_schur_without_room_for_split_links(W, dims):
+    """A budget that holds the call's own buffers but not the extra copy of
+    the links: the same result, bit for bit."""
+    U = I.random_gauge(dims, 0.5, 1)
+    psi = I.gaussian_source(dims, 4)
+    got, used = {}, {}
+    for prec in (W.F64, W.F32):
+        for budget in (0, 1):
+            # 1680 bytes a site resident (links and clover), up to 672 for the
+            # call, 192 staged by unpack
+            ctx = W.Context(0, hbm_budget=budget * (2700 * I.volume(dims) + 65536))
+            lat = W.Lattice(ctx, dims, BC)
+            lat.upload_gauge(U)
+            out = lat.empty(prec)
+            lat.apply_schur(prec, 0.126, 1.3, lat.pack(psi, prec), out)
+            got[prec, budget] = lat.unpack(out, prec)
+            used[prec, budget] = ctx.bytes_in_use()
+            lat.close()
+            ctx.close()
+        assert used[prec, 1] < used[prec, 0]
+        assert np.array_equal(got[prec, 0], got[prec, 1])
