@@ -962,7 +962,7 @@ struct SiteFieldsDot {
     template <int MU>
     WCL_DEV float uk(int k) const { return (float)((k & 1) ? u[MU][k >> 1].y : u[MU][k >> 1].x); }
     WCL_DEV float ck_(int k) const { return (float)((k & 1) ? c[k >> 1].y : c[k >> 1].x); }
-    WCL_DEV void load(const BlockArgs& a, int gi) {
+    WCL_DEV void load_links(const BlockArgs& a, int gi) {
         const h4v* gp = (const h4v*)a.gauge;
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
@@ -981,6 +981,15 @@ struct SiteFieldsDot {
 #pragma unroll
             for (int k = 0; k < 3; ++k) u[mu][6 + k] = pack2(t[12 + 2 * k], t[12 + 2 * k + 1]);
         }
+    }
+    // U_mu(x) times -1 where neg: the fermion boundary phase of the hop
+    // between x and x + mu, in either direction
+    WCL_DEV void negate_link(int mu, bool neg) {
+        const unsigned m = neg ? 0x80008000u : 0u;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) u[mu][k] = __builtin_bit_cast(h2v, __builtin_bit_cast(unsigned, u[mu][k]) ^ m);
+    }
+    WCL_DEV void load_clover(const BlockArgs& a, int gi) {
         const h8v* cp = (const h8v*)a.clover;
 #pragma unroll
         for (int g = 0; g < 9; ++g) {
@@ -1117,17 +1126,26 @@ struct FusedFields<WCL_F16, true> {
 // domain), src being the previous sweep's final MR residual (no overlap).
 // DOT: each site keeps its own rho in registers and publishes it to the
 // neighbours as binary16 pairs, with the backward terms as binary16 pairs
-// (36 instead of 72 LDS words per site).  Three domains per CU would then
-// fit the LDS but not the registers: forced to 168 VGPRs the kernel spills
-// and ran slower, so it keeps two.
-template <bool DOT>
+// (36 instead of 72 LDS words per site).
+//
+// With two domains per CU (two waves per SIMD) the loads of one domain and
+// the steps of the other overlapped badly: a 32^4 sweep took the sum of its
+// bytes' time and its steps' time.  Three fit when 16 of the 24 components of
+// the solution sit in LDS between steps (52 words per site, 3 x 52 KB of 160),
+// the neighbour indices are packed into 3 registers, the boundary phases are
+// folded into the links, and the clover is loaded only after the residual
+// update: 162-167 VGPRs, no spill (193 before).  First / later sweep of 4 steps
+// at 32^4: 195 / 248 -> 175 / 217 us; NRAS 5: 1183 -> 1040 us.  RES == 1 (overlap)
+// needs the clover during its residual update and keeps two.
+template <bool DOT, int RES>
 struct FusedShape {
-    static constexpr int lds_words = DOT ? 36 : 72;
-    static constexpr int min_waves = WCL_FUSED_MINWAVES;
+    static constexpr int xl = DOT ? 16 : 0;   // components of the solution kept in LDS
+    static constexpr int lds_words = DOT ? 36 + xl : 72;
+    static constexpr int min_waves = DOT && RES != 1 ? 3 : WCL_FUSED_MINWAVES;
 };
 
 template <int GP, int SRC, int VP, int NT, int RES, bool DOT>
-__global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(BlockArgs a, int write_vj) {
+__global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_fused(BlockArgs a, int write_vj) {
     extern __shared__ float lds[];
     float* s_rho = lds;                 // [24][NT]
     float* s_bwd = lds + 24 * NT;       // [4][12][NT] FP32, or [4][6][NT] binary16 pairs (DOT)
@@ -1153,7 +1171,15 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
         block_site(a.g, a.B, blk, l, lc, x);
         gi = geom_index(a.g, x);
         SpinorIO<SRC>::load((const char*)a.src + rhs * a.src_stride, a.g.V, gi, rho);   // projection P r
-        F.load(a, gi);
+        if constexpr (DOT) {
+            F.load_links(a, gi);
+#pragma unroll
+            for (int mu = 0; mu < 4; ++mu)
+                if (a.g.bc[mu] < 0) F.negate_link(mu, x[mu] == a.g.L[mu] - 1);
+            if constexpr (RES == 1) F.load_clover(a, gi);
+        } else {
+            F.load(a, gi);
+        }
     }
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -1198,6 +1224,7 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
         spin_project<(K) / 2, (K) % 2 == 0>(s, h);                                        \
         if ((K) % 2 == 0) {                                                               \
             F.template apply<(K) / 2, false>(h, w);                                       \
+            if (DOT) ph[K] = 1.f; /* in the link */                                       \
         } else {                                                                          \
             GaugeIO<GP>::template load<false>(a.gauge, a.g.V, (K) / 2, lnk[K], u);        \
             su3_apply2<true>(u, h, w);                                                    \
@@ -1233,6 +1260,7 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
         spin_project<(K) / 2, (K) % 2 == 0>(s, h);                                    \
         if ((K) % 2 == 0) {                                                           \
             F.template apply<(K) / 2, false>(h, w);                                   \
+            if (DOT) ph[K] = 1.f; /* in the link */                                   \
         } else {                                                                      \
             GaugeIO<GP>::template load<false>(a.gauge, a.g.V, (K) / 2, lnk[K], u);    \
             su3_apply2<true>(u, h, w);                                                \
@@ -1246,6 +1274,11 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
             if (a.rout && block_owned(a.B, lc))
                 SpinorIO<VP>::store((char*)a.rout + rhs * a.rout_stride, a.g.V, gi, rho);
         }
+    }
+    if constexpr (DOT && RES != 1) {
+        // not before: the residual update needs the registers
+        __builtin_amdgcn_sched_barrier(0);
+        if (active) F.load_clover(a, gi);
     }
     // binary16 operands: scale the domain's rho by 2^-e, 2^e near its RMS
     // component (exact in FP32; the solution and the final residual are
@@ -1274,8 +1307,23 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
         // own rho in registers (FP32); the neighbours read its binary16 pairs
         h2v* s_rp = (h2v*)lds;               // [12][NT]
         h2v* s_bw = (h2v*)(lds + 12 * NT);   // [4][6][NT]
+        constexpr int XL = FusedShape<DOT, RES>::xl;
+        f4v* s_xs = (f4v*)(lds + 36 * NT);   // [XL / 4][NT]
+#pragma unroll
+        for (int g = 0; g < XL / 4; ++g) s_xs[g * NT + l] = f4v{0.f, 0.f, 0.f, 0.f};
+        // the neighbours' local indices, one byte each (forward in nbrs[0],
+        // backward in nbrs[1]), and a bit for each that exists: 3 registers
+        // for 8, unpacked again in every step
+        unsigned nbrs[2] = {0u, 0u}, have = 0u;
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu) {
+            nbrs[0] |= (unsigned)(nf[mu] & 255) << (8 * mu);
+            nbrs[1] |= (unsigned)(nb[mu] & 255) << (8 * mu);
+            have |= (nf[mu] >= 0 ? 1u : 0u) << mu | (nb[mu] >= 0 ? 16u : 0u) << mu;
+        }
         for (int step = 0; step < a.B.n_dominv; ++step) {
             F.refresh();
+            asm volatile("" : "+v"(nbrs[0]), "+v"(nbrs[1]), "+v"(have));
             h2v rp[12];
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
@@ -1304,22 +1352,24 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
             float q[24];
             F.site_term16(rp, rho, ck, q);
 #define WCL_HOPS16(MU)                                                                           \
-    if (nf[MU] >= 0) {                                                                           \
+    if (have & (1u << (MU))) {                                                                   \
+        const int n = (nbrs[0] >> (8 * (MU))) & 255;                                             \
         h2v np[12], ha[6], hb[6];                                                                \
         float w[12];                                                                             \
-        _Pragma("unroll") for (int k = 0; k < 12; ++k) np[k] = s_rp[k * NT + nf[MU]];           \
+        _Pragma("unroll") for (int k = 0; k < 12; ++k) np[k] = s_rp[k * NT + n];                \
         spin_project16<MU, true, false>(np, ha, hb);                                             \
         F.template apply16<MU, false>(ha, hb, w);                                                \
-        spin_accumulate<MU, true>(w, mk * phf[MU], q);                                           \
+        spin_accumulate<MU, true>(w, mk, q);                                                     \
     }                                                                                            \
-    if (nb[MU] >= 0) {                                                                           \
+    if (have & (16u << (MU))) {                                                                  \
+        const int n = (nbrs[1] >> (8 * (MU))) & 255;                                             \
         float w[12];                                                                             \
         _Pragma("unroll") for (int k = 0; k < 6; ++k) {                                          \
-            const h2v t = s_bw[(MU * 6 + k) * NT + nb[MU]];                                      \
+            const h2v t = s_bw[(MU * 6 + k) * NT + n];                                           \
             w[2 * k] = (float)t.x;                                                               \
             w[2 * k + 1] = (float)t.y;                                                           \
         }                                                                                        \
-        spin_accumulate<MU, false>(w, mk * phb[MU], q);                                          \
+        spin_accumulate<MU, false>(w, mk, q);                                                    \
     }
             WCL_HOPS16(0) WCL_HOPS16(1) WCL_HOPS16(2) WCL_HOPS16(3)
 #undef WCL_HOPS16
@@ -1347,6 +1397,14 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
             const double inv = d[2] > 0 ? 1.0 / d[2] : 0.0;
             const float ar = (float)(d[0] * inv), ai = (float)(d[1] * inv);
 #pragma unroll
+            for (int g = 0; g < XL / 4; ++g) {
+                const f4v t = s_xs[g * NT + l];
+                xs[4 * g] = t.x;
+                xs[4 * g + 1] = t.y;
+                xs[4 * g + 2] = t.z;
+                xs[4 * g + 3] = t.w;
+            }
+#pragma unroll
             for (int k = 0; k < 12; ++k) {
                 const float pr = rho[2 * k], pi = rho[2 * k + 1];
                 xs[2 * k] = fmad(ar, pr, xs[2 * k]);
@@ -1356,6 +1414,17 @@ __global__ __launch_bounds__(NT, FusedShape<DOT>::min_waves) void k_blk_fused(Bl
                 rho[2 * k] = fmad(ai, q[2 * k + 1], fmad(-ar, q[2 * k], pr));
                 rho[2 * k + 1] = fmad(-ai, q[2 * k], fmad(-ar, q[2 * k + 1], pi));
             }
+#pragma unroll
+            for (int g = 0; g < XL / 4; ++g)
+                s_xs[g * NT + l] = f4v{xs[4 * g], xs[4 * g + 1], xs[4 * g + 2], xs[4 * g + 3]};
+        }
+#pragma unroll
+        for (int g = 0; g < XL / 4; ++g) {
+            const f4v t = s_xs[g * NT + l];
+            xs[4 * g] = t.x;
+            xs[4 * g + 1] = t.y;
+            xs[4 * g + 2] = t.z;
+            xs[4 * g + 3] = t.w;
         }
     } else {
     // rho lives in LDS between steps: only its owner thread writes it
@@ -1507,7 +1576,7 @@ int fused_threads(int ev) { return ev <= 256 ? 256 : 0; }
 
 template <int GP, int SRC, int VP, int NT, int RES, bool DOT>
 static int launch_fused_t(const BlockArgs& a, hipStream_t st) {
-    const size_t lds = (size_t)FusedShape<DOT>::lds_words * NT * sizeof(float);
+    const size_t lds = (size_t)FusedShape<DOT, RES>::lds_words * NT * sizeof(float);
     // dynamic LDS above the 64 KB default; set once per instantiation (thread-safe static)
     static const hipError_t attr = hipFuncSetAttribute((const void*)k_blk_fused<GP, SRC, VP, NT, RES, DOT>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
