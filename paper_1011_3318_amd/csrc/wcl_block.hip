@@ -1118,6 +1118,123 @@ struct FusedFields<WCL_F16, true> {
     using type = SiteFieldsDot;
 };
 
+// One crossing hop's data as stored: the neighbour's spinor (12 binary16 pairs
+// and its scale) and, for a backward hop, rows 0 and 1 of its link.
+struct CrossBuf {
+    h2v s[12];
+    float sc;
+    h2v u[6];
+};
+
+// Requests the data of crossing hop K.  Every lane loads, lanes without the
+// hop at site 0: the loads stay outside divergent branches, so that the next
+// hop's are in flight while this one is computed.
+template <int K>
+WCL_DEV void cross_load(const BlockArgs& a, const char* vp, int n, CrossBuf& c) {
+    c.sc = load_spinor16(vp, a.g.V, n, c.s);
+    if constexpr (K % 2 == 1) {
+        const h4v* gp = (const h4v*)a.gauge;
+#pragma unroll
+        for (int g = 0; g < 3; ++g) {
+            const h4v v = gp[tix(3 * (K / 2) + g, n, 12)];
+            c.u[2 * g] = h2v{v.x, v.y};
+            c.u[2 * g + 1] = h2v{v.z, v.w};
+        }
+    }
+}
+
+// spin_project of a spinor as stored: h = u sc +- l sc, the lower spins'
+// products rounded and the upper ones' inside an FMA.
+template <int MU, bool FWD>
+WCL_DEV void spin_project_scaled(const h2v s[12], float sc, float h[12]) {
+    const float sg = FWD ? 1.f : -1.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const h2v u0 = s[c], u1 = s[3 + c];
+        const float l0r = (float)s[6 + c].x * sc, l0i = (float)s[6 + c].y * sc;
+        const float l1r = (float)s[9 + c].x * sc, l1i = (float)s[9 + c].y * sc;
+        float a0, b0, a1, b1;   // the lower spins' part of (h0, h1), re and im
+        if (MU == 0) {
+            a0 = -sg * l1i;
+            b0 = sg * l1r;
+            a1 = -sg * l0i;
+            b1 = sg * l0r;
+        } else if (MU == 1) {
+            a0 = sg * l1r;
+            b0 = sg * l1i;
+            a1 = -sg * l0r;
+            b1 = -sg * l0i;
+        } else if (MU == 2) {
+            a0 = -sg * l0i;
+            b0 = sg * l0r;
+            a1 = sg * l1i;
+            b1 = -sg * l1r;
+        } else {
+            a0 = sg * l0r;
+            b0 = sg * l0i;
+            a1 = sg * l1r;
+            b1 = sg * l1i;
+        }
+        h[2 * c] = fmad((float)u0.x, sc, a0);
+        h[2 * c + 1] = fmad((float)u0.y, sc, b0);
+        h[6 + 2 * c] = fmad((float)u1.x, sc, a1);
+        h[7 + 2 * c] = fmad((float)u1.y, sc, b1);
+    }
+}
+
+template <int K, bool DOT, typename FF>
+WCL_DEV void cross_hop(const FF& F, const CrossBuf& c, float mk, float ph, float acc[24]) {
+    float h[12], w[12];
+    spin_project_scaled<K / 2, K % 2 == 0>(c.s, c.sc, h);
+    if constexpr (K % 2 == 0) {
+        F.template apply<K / 2, false>(h, w);
+    } else {
+        float u[18];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            u[2 * k] = (float)c.u[k].x;
+            u[2 * k + 1] = (float)c.u[k].y;
+        }
+        reconstruct_row2(u);
+        su3_apply2<true>(u, h, w);
+    }
+    // DOT: the own links carry the boundary phase already
+    spin_accumulate<K / 2, K % 2 == 0>(w, DOT && K % 2 == 0 ? mk : mk * ph, acc);
+}
+
+// rho -= the hops of D vprev that leave the domain (FP16 storage), two hops'
+// loads in flight.  Bound by the latency of those loads: with each hop's loads
+// inside its own divergent branch, a later sweep at 32^4 took 217 us (binary16
+// operands) and 272 us (FP32 arithmetic), pipelined 209 and 262; at 8^4 26.1
+// and 27.9, pipelined 25.2 and 26.4.
+template <bool DOT, typename FF>
+WCL_DEV void crossing_hops16(const BlockArgs& a, const FF& F, int rhs, int gi, const int x[4], bool active,
+                             const int nf[4], const int nb[4], float mk, float rho[24]) {
+    const char* vp = (const char*)a.vprev + rhs * a.vprev_stride;
+    int nbr[8], lnk[8];
+    float ph[8];
+    hop_sites(a.g, gi, x, nbr, lnk, ph);
+    bool cr[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        cr[k] = active && (k % 2 == 0 ? nf[k / 2] : nb[k / 2]) < 0;
+        nbr[k] = cr[k] ? nbr[k] : 0;
+    }
+    float acc[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = 0.f;
+    CrossBuf c0, c1;
+    cross_load<0>(a, vp, nbr[0], c0);
+#define WCL_XHOP(K, C, N)                                                       \
+    if constexpr ((K) < 7) cross_load<((K) + 1) & 7>(a, vp, nbr[((K) + 1) & 7], N); \
+    if (cr[K]) cross_hop<K, DOT>(F, C, mk, ph[K], acc);
+    WCL_XHOP(0, c0, c1) WCL_XHOP(1, c1, c0) WCL_XHOP(2, c0, c1) WCL_XHOP(3, c1, c0)
+    WCL_XHOP(4, c0, c1) WCL_XHOP(5, c1, c0) WCL_XHOP(6, c0, c1) WCL_XHOP(7, c1, c0)
+#undef WCL_XHOP
+#pragma unroll
+    for (int k = 0; k < 24; ++k) rho[k] -= acc[k];
+}
+
 #ifndef WCL_FUSED_MINWAVES
 #define WCL_FUSED_MINWAVES 2
 #endif
@@ -1135,7 +1252,7 @@ struct FusedFields<WCL_F16, true> {
 // the neighbour indices are packed into 3 registers, the boundary phases are
 // folded into the links, and the clover is loaded only after the residual
 // update: 162-167 VGPRs, no spill (193 before).  First / later sweep of 4 steps
-// at 32^4: 195 / 248 -> 175 / 217 us; NRAS 5: 1183 -> 1040 us.  RES == 1 (overlap)
+// at 32^4: 195 / 248 -> 172 / 209 us; NRAS 5: 1183 -> 1021 us.  RES == 1 (overlap)
 // needs the clover during its residual update and keeps two.
 template <bool DOT, int RES>
 struct FusedShape {
@@ -1209,7 +1326,9 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
         // the domain, and v_{j-1} = x there, so r_j = r_{j-1} - D v_{j-1} is
         // the previous sweep's final rho minus the hops of D v_{j-1} that
         // leave the domain (Dirichlet D_Omega drops exactly those).
-        if (active) {
+        if constexpr (VP == WCL_F16) {
+            crossing_hops16<DOT>(a, F, rhs, gi, x, active, nf, nb, mk, rho);
+        } else if (active) {
             const char* vp = (const char*)a.vprev + rhs * a.vprev_stride;
             int nbr[8], lnk[8];
             float ph[8];
