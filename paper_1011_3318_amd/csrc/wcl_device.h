@@ -569,9 +569,38 @@ WCL_DEV void load_link16(const void* gauge, int V, int mu, int site, float z, h2
     }
 }
 
-// acc = A(x) psi = sc psi + ck cs sc C psi: psi as stored (12 binary16 pairs,
-// scale sc), C the stored binary16 clover blocks (scale cs); the products
-// are exact binary16 products summed in FP32.
+// Block bk of acc = A(x) psi = sc psi + ck cs sc C psi: psi as stored (xp: its
+// 6 binary16 pairs of the block, scale sc), C the stored binary16 clover blocks
+// (cv, scale cs); f = ck cs sc; the products are exact binary16 products
+// summed in FP32.
+template <int bk>
+WCL_DEV void clover_block16(const h8v cv[9], const h2v xp[6], float sc, float f, float z, float acc[12]) {
+    // block bk: halves 36 bk + (6 diagonal reals, then 15 complex entries)
+    auto hv = [&](int k) { return cv[(36 * bk + k) / 8][(36 * bk + k) % 8]; };
+    float y[12];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        y[2 * a] = fmad((float)hv(a), (float)xp[a].x, z);
+        y[2 * a + 1] = fmad((float)hv(a), (float)xp[a].y, z);
+    }
+    int k = 0;
+#pragma unroll
+    for (int a = 0; a < 6; ++a)
+#pragma unroll
+        for (int b = a + 1; b < 6; ++b, ++k) {
+            const h2v C = h2v{hv(6 + 2 * k), hv(7 + 2 * k)};   // C_ab; C_ba = conj(C_ab)
+            y[2 * a] = dot2(C, cj(xp[b]), y[2 * a]);
+            y[2 * a + 1] = dot2(C, swp(xp[b]), y[2 * a + 1]);
+            y[2 * b] = dot2(C, xp[a], y[2 * b]);
+            y[2 * b + 1] = dot2(C, mul_mi(xp[a]), y[2 * b + 1]);
+        }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+        acc[2 * a] = fmad(f, y[2 * a], fmad((float)xp[a].x, sc, z));
+        acc[2 * a + 1] = fmad(f, y[2 * a + 1], fmad((float)xp[a].y, sc, z));
+    }
+}
+
 template <bool NT>
 WCL_DEV void clover_site16(const void* base, int V, int i, const h2v x16[12], float sc, float ck, float z,
                            float acc[24]) {
@@ -580,34 +609,8 @@ WCL_DEV void clover_site16(const void* base, int V, int i, const h2v x16[12], fl
 #pragma unroll
     for (int g = 0; g < 9; ++g) cv[g] = ldx<NT>(p + tix(g, i, 9));
     const float f = ck * sc * ((const float*)((const char*)base + half_clover_scale_offset(V)))[i];
-#pragma unroll
-    for (int bk = 0; bk < 2; ++bk) {
-        // block bk: halves 36 bk + (6 diagonal reals, then 15 complex entries)
-        auto hv = [&](int k) { return cv[(36 * bk + k) / 8][(36 * bk + k) % 8]; };
-        const h2v* xp = x16 + 6 * bk;
-        float y[12];
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            y[2 * a] = fmad((float)hv(a), (float)xp[a].x, z);
-            y[2 * a + 1] = fmad((float)hv(a), (float)xp[a].y, z);
-        }
-        int k = 0;
-#pragma unroll
-        for (int a = 0; a < 6; ++a)
-#pragma unroll
-            for (int b = a + 1; b < 6; ++b, ++k) {
-                const h2v C = h2v{hv(6 + 2 * k), hv(7 + 2 * k)};   // C_ab; C_ba = conj(C_ab)
-                y[2 * a] = dot2(C, cj(xp[b]), y[2 * a]);
-                y[2 * a + 1] = dot2(C, swp(xp[b]), y[2 * a + 1]);
-                y[2 * b] = dot2(C, xp[a], y[2 * b]);
-                y[2 * b + 1] = dot2(C, mul_mi(xp[a]), y[2 * b + 1]);
-            }
-#pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            acc[12 * bk + 2 * a] = fmad(f, y[2 * a], fmad((float)xp[a].x, sc, z));
-            acc[12 * bk + 2 * a + 1] = fmad(f, y[2 * a + 1], fmad((float)xp[a].y, sc, z));
-        }
-    }
+    clover_block16<0>(cv, x16, sc, f, z, acc);
+    clover_block16<1>(cv, x16 + 6, sc, f, z, acc + 12);
 }
 
 // acc += f * (w0, w1, lower(w)) for the projection spin_project<MU,FWD>.

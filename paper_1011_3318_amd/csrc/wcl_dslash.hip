@@ -485,6 +485,191 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy16(DslashArgs
     }
 }
 
+// ------------------------------------------------------- small launches
+// One wavefront per 64 sites and direction: wavefront mu of a workgroup takes
+// the two hops of direction mu (and, for mu < 2, clover block mu) of the same
+// 64 sites, all their loads in flight at once, and the four partial sums meet
+// in LDS, where each wavefront finishes a quarter of the components.  For
+// launches that leave most SIMDs idle, where the time is one wavefront's chain
+// of loads and arithmetic: this has a quarter of that chain.
+// A quarter of a spinor: components 3 w .. 3 w + 2 (6 reals), by storage.
+template <int P>
+struct SpinorQuarter;
+template <>
+struct SpinorQuarter<WCL_F64> {
+    WCL_DEV static void load(const void* base, int V, int i, int w, double s[6]) {
+        const d2v* p = (const d2v*)base;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const d2v v = p[tix(3 * w + j, i, 12)];
+            s[2 * j] = v.x;
+            s[2 * j + 1] = v.y;
+        }
+    }
+    WCL_DEV static void store(void* base, int V, int i, int w, const double s[6], double) {
+        d2v* p = (d2v*)base;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) p[tix(3 * w + j, i, 12)] = d2v{s[2 * j], s[2 * j + 1]};
+    }
+};
+template <>
+struct SpinorQuarter<WCL_F32> {
+    WCL_DEV static size_t at(int c, int i) { return 2 * tix(c >> 1, i, 6) + (c & 1); }
+    WCL_DEV static void load(const void* base, int V, int i, int w, float s[6]) {
+        const float2* p = (const float2*)base;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const float2 v = p[at(3 * w + j, i)];
+            s[2 * j] = v.x;
+            s[2 * j + 1] = v.y;
+        }
+    }
+    WCL_DEV static void store(void* base, int V, int i, int w, const float s[6], float) {
+        float2* p = (float2*)base;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) p[at(3 * w + j, i)] = float2{s[2 * j], s[2 * j + 1]};
+    }
+};
+template <>
+struct SpinorQuarter<WCL_F16> {
+    // m: the site's largest |component|
+    WCL_DEV static void store(void* base, int V, int i, int w, const float s[6], float m) {
+        const float inv = m > 0.f ? 1.0f / m : 0.f;
+        h2v* p = (h2v*)base;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int c = 3 * w + j;
+            p[4 * tix(c >> 2, i, 3) + (c & 3)] = pack2(s[2 * j] * inv, s[2 * j + 1] * inv);
+        }
+        if (w == 0) ((float*)((char*)base + half_spinor_scale_offset(V)))[i] = m;
+    }
+};
+
+template <int MU, int GP, int SPI, typename T>
+WCL_DEV void dslash_direction(const DslashArgs& a, const char* in, int i, T acc[24]) {
+    const int V = a.g.V;
+    int x[4];
+    geom_coords(a.g, i, x);
+    int y[4] = {x[0], x[1], x[2], x[3]};
+    const bool wf = x[MU] + 1 == a.g.L[MU], wb = x[MU] == 0;
+    y[MU] = wf ? 0 : x[MU] + 1;
+    const int nf = geom_index(a.g, y);
+    y[MU] = wb ? a.g.L[MU] - 1 : x[MU] - 1;
+    const int nb = geom_index(a.g, y);
+    const T mk = T(-a.kappa), bc = T(a.g.bc[MU]), ck = T(a.csw * a.kappa);
+    const T ff = wf ? mk * bc : mk, fb = wb ? mk * bc : mk;
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = T(0);
+    if constexpr (GP == WCL_F16 && SPI == WCL_F16) {
+        float z = 0.f;   // opaque zero: the first product of every chain stays a v_dot2
+        asm volatile("" : "+v"(z));
+        h2v sf[12], sb[12], uf[9], ub[9];
+        const float cf = load_spinor16(in, V, nf, sf), cb = load_spinor16(in, V, nb, sb);
+        if constexpr (MU < 2) {
+            h2v s[12];
+            h8v cv[9];
+            const float sc = load_spinor16(in, V, i, s);
+            const h8v* p = (const h8v*)a.clover;
+#pragma unroll
+            for (int g = 4 * MU; g < 4 * MU + 5; ++g) cv[g] = p[tix(g, i, 9)];
+            const float f = ck * sc * ((const float*)((const char*)a.clover + half_clover_scale_offset(V)))[i];
+            load_link16<false>(a.gauge, V, MU, i, z, uf);
+            load_link16<false>(a.gauge, V, MU, nb, z, ub);
+            clover_block16<MU>(cv, s + 6 * MU, sc, f, z, acc + 12 * MU);
+        } else {
+            load_link16<false>(a.gauge, V, MU, i, z, uf);
+            load_link16<false>(a.gauge, V, MU, nb, z, ub);
+        }
+        hop_compute16<MU, true>(sf, uf, ff * cf, z, acc);
+        hop_compute16<MU, false>(sb, ub, fb * cb, z, acc);
+    } else {
+        typename SpinorIO<SPI>::Stored sf[24], sb[24];
+        T uf[18], ub[18];
+        const T cf = SpinorIO<SPI>::load_s(in, V, nf, sf);
+        GaugeIO<GP>::template load_raw<false>(a.gauge, V, MU, i, uf);
+        const T cb = SpinorIO<SPI>::load_s(in, V, nb, sb);
+        GaugeIO<GP>::template load_raw<false>(a.gauge, V, MU, nb, ub);
+        if constexpr (MU < 2) {
+            T s[24], c[36], w[12];
+            SpinorIO<SPI>::load(in, V, i, s);
+            CloverBlk<GP>::template load<false>(a.clover, V, i, MU, c);
+            herm6_apply(c, s + 12 * MU, w);
+#pragma unroll
+            for (int j = 0; j < 12; ++j) acc[12 * MU + j] = s[12 * MU + j] + ck * w[j];
+        }
+        hop_compute<MU, true>(sf, uf, ff * cf, acc);
+        hop_compute<MU, false>(sb, ub, fb * cb, acc);
+    }
+}
+
+template <int GP, int SPI, int SPO, int EPI, int SPY>
+__global__ __launch_bounds__(256, GP == WCL_F64 ? 2 : 4) void k_dslash_w4(DslashArgs a) {
+    using T = typename Real<GP>::T;
+    static_assert(EPI != DS_AXPY || SPO != WCL_F16, "the RAS residual update keeps one lane per site");
+    __shared__ T part[4][24][64];
+    __shared__ float smax[4][64];
+    const int tiles = gridDim.x / a.nrhs;
+    const int rhs = blockIdx.x % a.nrhs, tile = blockIdx.x / a.nrhs;
+    if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int i = tile * 64 + l, V = a.g.V;
+    const bool active = i < V;
+    if (active) {
+        const char* in = (const char*)a.in + rhs * a.in_stride;
+        T acc[24];
+        switch (w) {
+            case 0: dslash_direction<0, GP, SPI>(a, in, i, acc); break;
+            case 1: dslash_direction<1, GP, SPI>(a, in, i, acc); break;
+            case 2: dslash_direction<2, GP, SPI>(a, in, i, acc); break;
+            default: dslash_direction<3, GP, SPI>(a, in, i, acc); break;
+        }
+#pragma unroll
+        for (int k = 0; k < 24; ++k) part[w][k][l] = acc[k];
+    }
+    __syncthreads();
+    T v[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const int c = 6 * w + k;
+        v[k] = (part[0][c][l] + part[1][c][l]) + (part[2][c][l] + part[3][c][l]);
+    }
+    if constexpr (EPI == DS_AXPY) {
+        if (active) {
+            T y[6];
+            SpinorQuarter<SPY>::load((const char*)a.y + rhs * a.y_stride, V, i, w, y);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[k] = y[k] - v[k];
+        }
+    }
+    T m = T(0);
+    if constexpr (SPO == WCL_F16) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) m = fmaxf(m, fabsf(v[k]));
+        smax[w][l] = m;
+        __syncthreads();
+        m = fmaxf(fmaxf(smax[0][l], smax[1][l]), fmaxf(smax[2][l], smax[3][l]));
+    }
+    if (active) SpinorQuarter<SPO>::store((char*)a.out + rhs * a.out_stride, V, i, w, v, m);
+    if constexpr (EPI == DS_DOT) {
+        double d[3] = {0.0, 0.0, 0.0};
+        if (active) {
+            T b[6], s0 = 0, s1 = 0, s2 = 0;
+            SpinorQuarter<SPO>::load((const char*)a.a + rhs * a.a_stride, V, i, w, b);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const T ar = b[2 * k], ai = b[2 * k + 1], br = v[2 * k], bi = v[2 * k + 1];
+                s0 = fmad(ai, bi, fmad(ar, br, s0));
+                s1 = fmad(-ai, br, fmad(ar, bi, s1));
+                s2 = fmad(bi, bi, fmad(br, br, s2));
+            }
+            d[0] = s0;
+            d[1] = s1;
+            d[2] = s2;
+        }
+        block_reduce3(d, a.partial + 3 * ((size_t)tile + (size_t)rhs * tiles));
+    }
+}
+
 // ------------------------------------------------ several lanes per site
 // Stores the float groups of s that belong to `lane` of LPS lanes.
 template <int P>
@@ -628,11 +813,27 @@ static size_t dslash_launch_bytes(int V, int gp, int spi, int spo) {
     return gauge_bytes(gp, V) + clover_bytes(gp, V) + spinor_rhs_bytes(spi, V) + spinor_rhs_bytes(spo, V);
 }
 
+// One wavefront per direction up to 4096 sites (256 wavefronts of a lattice:
+// one per CU).  Kernel time at 8^4, one lane per site / one wavefront per
+// direction: FP32 6.6 / 4.7 us, with the dot products 8.6 / 5.8, FP64 12.0 / 7.3.
+// Past that the fourfold wavefronts no longer find idle SIMDs (12^4 with 4 rhs
+// FP32 12.0 / 13.4 us per call, 12 rhs 22 / 28; 12x12x18x20 FP32 9.7 / 11.9).
+// The rule looks at the volume only: a batched right-hand side gets the bits
+// of its own single launch.
+static bool dslash_small(int V, int lps) { return lps == 1 && V <= 4096; }
+
 template <int GP, int SPI, int SPO, int EPI, int SPY>
 static int launch_t(const DslashArgs& a0, hipStream_t st) {
     DslashArgs a = a0;
     a.walk = tile_walk(a.g, 1);
-    const int tiles = dslash_partials_per_rhs(a.g.V, a.lps);
+    if constexpr (EPI != DS_AXPY || SPO != WCL_F16)
+        if (dslash_small(a.g.V, a.lps)) {
+            const int n = (a.g.V + 63) / 64 * a.nrhs;
+            k_dslash_w4<GP, SPI, SPO, EPI, SPY><<<n, 256, 0, st>>>(a);
+            WCL_HIP(hipGetLastError());
+            return WCL_OK;
+        }
+    const int tiles = (a.g.V + 256 / a.lps - 1) / (256 / a.lps);
     switch (a.lps) {
         case 2: k_dslash_ml<GP, SPI, SPO, EPI, SPY, 2><<<tiles * a.nrhs, 256, 0, st>>>(a); break;
         case 4: k_dslash_ml<GP, SPI, SPO, EPI, SPY, 4><<<tiles * a.nrhs, 256, 0, st>>>(a); break;
@@ -660,9 +861,9 @@ static int launch_t(const DslashArgs& a0, hipStream_t st) {
     return WCL_OK;
 }
 
-// workgroups (= dot-product partial sums) per rhs for lps lanes per site
+// workgroups (= dot-product partial sums) per rhs
 int dslash_partials_per_rhs(int V, int lps) {
-    const int spw = 256 / (lps == 2 || lps == 4 ? lps : 1);
+    const int spw = dslash_small(V, lps) ? 64 : 256 / lps;
     return (V + spw - 1) / spw;
 }
 

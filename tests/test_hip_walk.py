@@ -1,5 +1,5 @@
 """Launches that walk the lattice's tiles in another order than they are
-stored (columns cut in x or y), and the parity-split fields of the even-odd
+stored (columns cut in x or y), launches on small lattices, and the parity-split fields of the even-odd
 operator with and without room for the split links, against the oracle."""
 import numpy as np
 import pytest
@@ -44,6 +44,31 @@ def test_walk_matches_oracle(W, dims):
         out = lat.empty(prec, 2)
         got = lat.unpack(lat.apply_schur(prec, kappa, csw, lat.pack(psi, prec, 2), out, nrhs=2), prec, 2)
         assert max(rel_err(got[k], o.apply_schur(psi[k], kappa, csw)) for k in range(2)) <= tol
+    lat.close()
+    ctx.close()
+
+
+# launches with one wavefront per direction: less than a tile, a last tile of
+# 4 sites, the largest lattice that takes them, and the next that does not
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 5, 13, 2), (8, 8, 8, 8), (8, 9, 8, 8)])
+def test_small_launches(W, dims):
+    ctx = W.Context(0)
+    U = I.random_gauge(dims, 0.5, 1)
+    lat = W.Lattice(ctx, dims, BC)
+    lat.upload_gauge(U)
+    o = Oracle(dims, U, bc=BC)
+    psi = I.gaussian_source(dims, 4, nrhs=3)
+    ref = [o.apply_D(psi[k], 0.126, 1.3) for k in range(3)]
+    for prec, tol in ((W.F64, 1e-13), (W.F32, 1e-5), (W.F16, 2e-3)):
+        got = lat.unpack(lat.apply_D(prec, 0.126, 1.3, lat.pack(psi, prec, 3), lat.empty(prec, 3), nrhs=3), prec, 3)
+        assert max(rel_err(got[k], ref[k]) for k in range(3)) <= tol
+        one = lat.unpack(lat.apply_D(prec, 0.126, 1.3, lat.pack(psi[2], prec), lat.empty(prec)), prec)
+        assert np.array_equal(one, got[2])
+    # the dot-product epilogue and the residual: a plain solve
+    phi = lat.empty(W.F64)
+    rc, st = lat.solve_bicgstab_f64(1e-11, 500, 0.11, 1.0, lat.pack(psi[0], W.F64), phi)
+    sol = lat.unpack(phi, W.F64)
+    assert rel_err(o.apply_D(sol, 0.11, 1.0), psi[0]) <= 1e-10
     lat.close()
     ctx.close()
 
