@@ -117,14 +117,18 @@ def check(rc: int, what: str = ""):
 
 def _stream(stream):
     if stream is None:
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the handle behind torch.cuda.current_stream(), without the Stream
+        # object (2.9 us of a 7.1 us D-apply call at 8^4)
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, torch.cuda.Stream):
-        return C.c_void_p(stream.cuda_stream)
-    return C.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 class Context:
