@@ -101,11 +101,13 @@ int wcl_init(int device, uint64_t hbm_budget_bytes, wcl_ctx** out) {
         delete c;
         return rc;
     }
+    stage_ref();
     *out = c;
     return WCL_OK;
 }
 
 int wcl_finalize(wcl_ctx* ctx) {
+    if (ctx) stage_unref();
     delete ctx;
     return WCL_OK;
 }
@@ -258,10 +260,7 @@ int wcl_upload_gauge(wcl_lattice* lat, const double* U) {
         return rc;
     }
     *lat->link_flag = 0;
-    if (hipMemcpy(stage, U, bytes, hipMemcpyHostToDevice) != hipSuccess) {
-        wcl_set_error("wcl_upload_gauge: host->device copy failed");
-        rc = WCL_EHIP;
-    }
+    rc = stage_to_device(lat->ctx->device, stage, U, bytes, 0);
     // 0.9e-12: below the tolerance 1e-12 by much more than the rounding of
     // the sums (1e-15), so an unflagged link passes the host's test too
     if (rc == WCL_OK) rc = launch_check_links(n, (const double*)stage, 0.9e-12, flag_dev, 0);
@@ -314,7 +313,7 @@ int wcl_upload_clover(wcl_lattice* lat, const double* C) {
     void* stage = nullptr;
     WCL_CHECK(wcl_dev_alloc(lat->ctx, &stage, bytes));
     int rc = WCL_OK;
-    if (hipMemcpy(stage, C, bytes, hipMemcpyHostToDevice) != hipSuccess) rc = WCL_EHIP;
+    rc = stage_to_device(lat->ctx->device, stage, C, bytes, 0);
     if (rc == WCL_OK) rc = launch_pack_clover(lat->g, (const double*)stage, lat->clover[0], lat->clover[1], lat->clover[2], 0);
     if (rc == WCL_OK && hipDeviceSynchronize() != hipSuccess) rc = WCL_EHIP;
     wcl_dev_free(lat->ctx, stage, bytes);
@@ -337,10 +336,7 @@ int wcl_download_clover(wcl_lattice* lat, double* C) {
     void* stage = nullptr;
     WCL_CHECK(wcl_dev_alloc(lat->ctx, &stage, bytes));
     int rc = launch_unpack_clover(lat->g, lat->clover[0], (double*)stage, 0);
-    if (rc == WCL_OK && hipMemcpy(C, stage, bytes, hipMemcpyDeviceToHost) != hipSuccess) {
-        wcl_set_error("wcl_download_clover: copy failed");
-        rc = WCL_EHIP;
-    }
+    if (rc == WCL_OK) rc = stage_to_host(lat->ctx->device, C, stage, bytes, 0);
     wcl_dev_free(lat->ctx, stage, bytes);
     return rc;
 }
@@ -380,7 +376,7 @@ int wcl_pack_spinor(wcl_lattice* lat, int prec, int nrhs, const double* host_aos
     WCL_CHECK(wcl_dev_alloc(lat->ctx, &stage, bytes));
     hipStream_t st = (hipStream_t)stream;
     int rc = WCL_OK;
-    if (hipMemcpyAsync(stage, host_aos, bytes, hipMemcpyHostToDevice, st) != hipSuccess) rc = WCL_EHIP;
+    rc = stage_to_device(lat->ctx->device, stage, host_aos, bytes, st);
     if (rc == WCL_OK) rc = wcl_pack_spinor_dev(lat, prec, nrhs, (const double*)stage, dev_soa, stream);
     if (hipStreamSynchronize(st) != hipSuccess && rc == WCL_OK) rc = WCL_EHIP;
     if (rc == WCL_EHIP) wcl_set_error("wcl_pack_spinor: copy or pack failed");
@@ -400,7 +396,7 @@ int wcl_unpack_spinor(wcl_lattice* lat, int prec, int nrhs, const void* dev_soa,
     WCL_CHECK(wcl_dev_alloc(lat->ctx, &stage, bytes));
     hipStream_t st = (hipStream_t)stream;
     int rc = wcl_unpack_spinor_dev(lat, prec, nrhs, dev_soa, (double*)stage, stream);
-    if (rc == WCL_OK && hipMemcpyAsync(host_aos, stage, bytes, hipMemcpyDeviceToHost, st) != hipSuccess) rc = WCL_EHIP;
+    if (rc == WCL_OK) rc = stage_to_host(lat->ctx->device, host_aos, stage, bytes, st);
     if (hipStreamSynchronize(st) != hipSuccess && rc == WCL_OK) rc = WCL_EHIP;
     if (rc == WCL_EHIP) wcl_set_error("wcl_unpack_spinor: unpack or copy failed");
     wcl_dev_free(lat->ctx, stage, bytes);

@@ -12,6 +12,15 @@ struct Scal {
     int active, breakdown;
 };
 
+// ------------------------------------------------- host transfers ------
+// Copies between host memory of the caller (pageable or not) and the device,
+// ordered on st (wcl_stage.cpp).  stage_to_device: the source may be changed on
+// return; stage_to_host: the destination is complete on return.
+int stage_to_device(int device, void* dev, const void* host, size_t bytes, hipStream_t st);
+int stage_to_host(int device, void* host, const void* dev, size_t bytes, hipStream_t st);
+void stage_ref();     // one per context: the staging memory is freed with the last
+void stage_unref();
+
 // order of the tiles in a launch, see walk_tile in wcl_device.h
 struct TileWalk {
     int tiles;   // 64-site tiles of one column at one t; 0: storage order

@@ -222,8 +222,7 @@ struct wcl_server {
         // the host sources go through one staging buffer, one after the other
         // (stream order keeps each copy behind the previous pack)
         for (int k = 0; k < n && rc == WCL_OK; ++k) {
-            if (hipMemcpyAsync(stage, js[k].req.eta_host, stage_b, hipMemcpyHostToDevice, s->st) != hipSuccess)
-                rc = WCL_EHIP;
+            rc = stage_to_device(ctx->device, stage, js[k].req.eta_host, stage_b, s->st);
             if (rc == WCL_OK)
                 rc = launch_pack_spinor(j.lat->g, WCL_F64, 1, (const double*)stage, (char*)eta + k * b64, b64, s->st);
         }
@@ -235,9 +234,7 @@ struct wcl_server {
             for (int k = 0; k < n && rc2 == WCL_OK; ++k) {
                 rc2 = launch_unpack_spinor(j.lat->g, WCL_F64, 1, (const char*)phi + k * b64, b64, (double*)stage,
                                            s->st);
-                if (rc2 == WCL_OK &&
-                    hipMemcpyAsync(js[k].req.phi_host, stage, stage_b, hipMemcpyDeviceToHost, s->st) != hipSuccess)
-                    rc2 = WCL_EHIP;
+                if (rc2 == WCL_OK) rc2 = stage_to_host(ctx->device, js[k].req.phi_host, stage, stage_b, s->st);
             }
             if (rc2 == WCL_OK && hipStreamSynchronize(s->st) != hipSuccess) rc2 = WCL_EHIP;
             if (rc2 != WCL_OK) rc = rc2;

@@ -178,7 +178,7 @@ class Lattice:
         check(lib.wcl_upload_clover(self.h, Cp.ctypes.data_as(C.POINTER(C.c_double))))
 
     def download_clover(self) -> np.ndarray:
-        out = np.zeros((self.V, 2, 36), dtype=np.float64)
+        out = np.empty((self.V, 2, 36), dtype=np.float64)
         check(lib.wcl_download_clover(self.h, out.ctypes.data_as(C.POINTER(C.c_double))))
         return out
 
@@ -203,7 +203,7 @@ class Lattice:
 
     def unpack(self, buf: torch.Tensor, prec: int, nrhs: int = 1, stream=None) -> np.ndarray:
         shape = (self.V, 4, 3) if nrhs == 1 else (nrhs, self.V, 4, 3)
-        out = np.zeros(shape, dtype=np.complex128)
+        out = np.empty(shape, dtype=np.complex128)   # written whole
         check(lib.wcl_unpack_spinor(self.h, prec, nrhs, _ptr(buf), out.ctypes.data_as(C.POINTER(C.c_double)),
                                     _stream(stream)))
         return out
@@ -224,7 +224,7 @@ class Lattice:
 
     def apply_D_blocks(self, ras: RasParams, kappa, csw, x: torch.Tensor, stream=None) -> np.ndarray:
         nb, ev = self.block_info(ras)
-        out = np.zeros((nb, ev, 4, 3), dtype=np.complex128)
+        out = np.empty((nb, ev, 4, 3), dtype=np.complex128)
         check(lib.wcl_apply_D_blocks(self.h, C.byref(ras), kappa, csw, _ptr(x),
                                      out.ctypes.data_as(C.POINTER(C.c_double)), _stream(stream)))
         return out

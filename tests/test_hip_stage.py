@@ -1,0 +1,70 @@
+"""Host transfers through the pinned staging chunks: sizes around the direct
+limit, a ragged last chunk, pinned sources, and several threads and streams at
+once (more than there are staging sets)."""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1011_3318_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def W():
+    from paper_1011_3318_amd import wcl
+    return wcl
+
+
+# bytes of the FP64 host field: 192 per site and rhs
+#   10x10x20x20  7.7 MB, below the direct limit of 8 MiB
+#   16x16x12x16  9.4 MB, three chunks, the last one ragged
+#   9x11x13x17 x 3  12.6 MB, odd extents
+@pytest.mark.parametrize("dims,nrhs", [((10, 10, 20, 20), 1), ((16, 16, 12, 16), 1), ((9, 11, 13, 17), 3)])
+@pytest.mark.parametrize("pinned", [False, True])
+def test_round_trip(W, dims, nrhs, pinned):
+    ctx = W.Context(0)
+    lat = W.Lattice(ctx, dims)
+    psi = I.gaussian_source(dims, 4, nrhs=nrhs)
+    if pinned:
+        t = torch.empty(psi.size * 2, dtype=torch.float64, pin_memory=True)
+        host = t.numpy().view(np.complex128).reshape(psi.shape)
+        host[...] = psi
+    else:
+        host = psi
+    dev = lat.pack(host, W.F64, nrhs)
+    assert np.array_equal(lat.unpack(dev, W.F64, nrhs), psi)
+    f32 = lat.unpack(lat.pack(host, W.F32, nrhs), W.F32, nrhs)
+    assert np.array_equal(f32, psi.astype(np.complex64).astype(np.complex128))
+    lat.close()
+    ctx.close()
+
+
+def test_many_threads_and_contexts(W):
+    """Six threads, each with its own context, lattice and stream."""
+    dims, bad = (16, 16, 12, 16), []
+    psis = [I.gaussian_source(dims, 10 + k) for k in range(6)]
+
+    def work(k):
+        try:
+            torch.cuda.set_device(0)
+            st = torch.cuda.Stream()
+            for rep in range(3):
+                ctx = W.Context(0)
+                lat = W.Lattice(ctx, dims)
+                dev = lat.pack(psis[k], W.F64, stream=st)
+                if not np.array_equal(lat.unpack(dev, W.F64, stream=st), psis[k]):
+                    bad.append((k, rep))
+                lat.close()
+                ctx.close()
+        except Exception as e:   # noqa: BLE001
+            bad.append((k, repr(e)))
+
+    th = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert bad == []
