@@ -842,23 +842,6 @@ WCL_DEV int xcd_remap(int b, int n) {
     return xcd < r ? xcd * (q + 1) + k : r * (q + 1) + (xcd - r) * q + k;
 }
 
-// Order in which a launch walks the 64-site tiles of a lattice field (or of
-// a half field, whose tiles hold the pairs of 128 sites).  Storage order runs
-// a column through all of t before the next one; when the cross-section is cut
-// in x or y too (extents such as 24: columns of 8 x 8 x 8), the x and y
-// neighbours outside the column are then a whole column away and every one of
-// them is fetched again after it left the L2.  The walk takes the columns of
-// one z range side by side instead: z range, t, (x, y) column, tile.
-// On 24^3x48 it fetches 1.12 instead of 1.37 GB per FP64 D-apply, 450 + 360
-// instead of 520 + 427 MB per FP32 Dhat.
-//
-// tile of walk position w
-WCL_DEV int walk_tile(const TileWalk& k, int w) {
-    if (k.tiles == 0) return w;
-    const int q = w / k.tiles, u = q / k.nxy, z = u / k.Lt;
-    return ((z * k.nxy + (q - u * k.nxy)) * k.Lt + (u - z * k.Lt)) * k.tiles + (w - q * k.tiles);
-}
-
 // This lane's element of the walk: workgroup wg of 256 lanes takes walk
 // positions 4 wg .. 4 wg + 3, one tile per wavefront.
 WCL_DEV int walk_site(const TileWalk& k, int wg) {

@@ -125,10 +125,10 @@ template <int GP, int SPI, int SPO, int EPI, int SPY, bool NT>
 __global__ __launch_bounds__(256, WCL_DSLASH_MINWAVES) void k_dslash(DslashArgs a) {
     using T = typename Real<GP>::T;
     static_assert((GP == WCL_F64) == (SPI == WCL_F64), "FP64 arithmetic needs FP64 spinors and links");
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int rhs = lb % a.nrhs;
+    int pos;
+    const int rhs = walk_rhs(a.walk, xcd_remap(blockIdx.x, gridDim.x), gridDim.x / a.nrhs, a.nrhs, &pos);
     if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
-    const int i = walk_site(a.walk, lb / a.nrhs);
+    const int i = walk_site(a.walk, pos);
     const bool active = i < a.g.V;
     T acc[24];
     if (active) {
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256, WCL_DSLASH_MINWAVES) void k_dslash(DslashArgs 
             SpinorIO<SPO>::load((const char*)a.a + rhs * a.a_stride, a.g.V, i, v);
             site_dot3(v, acc, d);
         }
-        block_reduce3(d, a.partial + 3 * (size_t)((lb / a.nrhs) + (size_t)rhs * (gridDim.x / a.nrhs)));
+        block_reduce3(d, a.partial + 3 * (size_t)((size_t)pos + (size_t)rhs * (gridDim.x / a.nrhs)));
     }
 }
 
@@ -207,11 +207,12 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy(DslashArgs a
     __shared__ T hb_y[12][256];   // U_y(s)^dag P+ psi(s): backward y hop of the row above
     const Geom& g = a.g;
     const int V = g.V;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int rhs = lb % a.nrhs;
+    int pos;
+    const int rhs = walk_rhs(a.walk, xcd_remap(blockIdx.x, gridDim.x), gridDim.x / a.nrhs, a.nrhs, &pos);
     if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
     const int t = threadIdx.x;
-    const int i = (lb / a.nrhs) * 256 + t;   // V % 256 == 0: every lane has a site
+    const int tile = walk_tile(a.walk, pos);
+    const int i = tile * 256 + t;   // V % 256 == 0: every lane has a site
     const char* in = (const char*)a.in + rhs * a.in_stride;
     const int R = g.c[0], NR = 256 / R;      // lanes per x row, rows per workgroup
     const int r = t >> g.lc[0];
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy(DslashArgs a
         T v[24];
         SpinorIO<SPO>::load((const char*)a.a + rhs * a.a_stride, V, i, v);
         site_dot3(v, acc, d);
-        block_reduce3(d, a.partial + 3 * (size_t)((lb / a.nrhs) + (size_t)rhs * (gridDim.x / a.nrhs)));
+        block_reduce3(d, a.partial + 3 * ((size_t)tile + (size_t)rhs * (gridDim.x / a.nrhs)));
     }
 }
 
@@ -353,11 +354,12 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy16(DslashArgs
     __shared__ float sc_y[256];      // psi(s)'s scale
     const Geom& g = a.g;
     const int V = g.V;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int rhs = lb % a.nrhs;
+    int pos;
+    const int rhs = walk_rhs(a.walk, xcd_remap(blockIdx.x, gridDim.x), gridDim.x / a.nrhs, a.nrhs, &pos);
     if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
     const int t = threadIdx.x;
-    const int i = (lb / a.nrhs) * 256 + t;   // V % 256 == 0: every lane has a site
+    const int tile = walk_tile(a.walk, pos);
+    const int i = tile * 256 + t;   // V % 256 == 0: every lane has a site
     const char* in = (const char*)a.in + rhs * a.in_stride;
     const int R = g.c[0], NR = 256 / R;      // lanes per x row, rows per workgroup
     const int r = t >> g.lc[0];
@@ -481,7 +483,7 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy16(DslashArgs
         float v[24];
         SpinorIO<SPO>::load((const char*)a.a + rhs * a.a_stride, V, i, v);
         site_dot3(v, acc, d);
-        block_reduce3(d, a.partial + 3 * (size_t)((lb / a.nrhs) + (size_t)rhs * (gridDim.x / a.nrhs)));
+        block_reduce3(d, a.partial + 3 * ((size_t)tile + (size_t)rhs * (gridDim.x / a.nrhs)));
     }
 }
 
@@ -825,7 +827,9 @@ static bool dslash_small(int V, int lps) { return lps == 1 && V <= 4096; }
 template <int GP, int SPI, int SPO, int EPI, int SPY>
 static int launch_t(const DslashArgs& a0, hipStream_t st) {
     DslashArgs a = a0;
-    a.walk = tile_walk(a.g, 1);
+    const bool xy = dslash_xy_layout(a.g);
+    a.walk = tile_walk(a.g, xy ? 256 : 64, 1, a.nrhs, site_vec_bytes(SPI) + site_vec_bytes(SPO), site_field_bytes(GP),
+                       xy);
     if constexpr (EPI != DS_AXPY || SPO != WCL_F16)
         if (dslash_small(a.g.V, a.lps)) {
             const int n = (a.g.V + 63) / 64 * a.nrhs;
@@ -841,7 +845,7 @@ static int launch_t(const DslashArgs& a0, hipStream_t st) {
             // non-temporal field loads only for one rhs streaming more than the
             // 256 MB Infinity Cache holds
             const bool nt = a.nrhs == 1 && dslash_launch_bytes(a.g.V, GP, SPI, SPO) > (256u << 20);
-            if (dslash_xy_layout(a.g)) {
+            if (xy) {
                 if constexpr (GP == WCL_F16 && SPI == WCL_F16) {
                     if (nt) k_dslash_xy16<SPO, EPI, SPY, true><<<tiles * a.nrhs, 256, 0, st>>>(a);
                     else k_dslash_xy16<SPO, EPI, SPY, false><<<tiles * a.nrhs, 256, 0, st>>>(a);

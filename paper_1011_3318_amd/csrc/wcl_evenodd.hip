@@ -108,8 +108,8 @@ WCL_DEV void eo_site(const EoArgs& a, int h, const T z[24], T y[24]) {
 template <int P, int MODE, int EPI, bool SL, bool FULL, bool NT, bool LINK_NT>
 __global__ __launch_bounds__(256, P == WCL_F64 ? 2 : 4) void k_eo(EoArgs a) {
     using T = typename Real<P>::T;
-    const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int rhs = lb % a.nrhs, tile = lb / a.nrhs;
+    int tile;
+    const int rhs = walk_rhs(a.walk, xcd_remap(blockIdx.x, gridDim.x), gridDim.x / a.nrhs, a.nrhs, &tile);
     if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
     const int h = walk_site(a.walk, tile);
     const bool active = h < a.Vh;
@@ -186,7 +186,7 @@ int eo_partials_per_rhs(int Vh) { return (Vh + 255) / 256; }
 template <int P, int MODE, int EPI, bool SL, bool FULL>
 static int launch_eo_n(const EoArgs& a0, hipStream_t st) {
     EoArgs a = a0;
-    a.walk = tile_walk(a.g, 2);
+    a.walk = tile_walk(a.g, 64, 2, a.nrhs, 2 * site_vec_bytes(P), site_field_bytes(P), false);
     const int grid = (a.Vh + 255) / 256 * a.nrhs;
     // Non-temporal field loads only for one rhs streaming more than the 256 MB
     // Infinity Cache holds.  A launch reads each split link once, the next

@@ -134,6 +134,9 @@ __host__ __device__ inline size_t tix(int k, int i, int NC) {
 inline size_t round_up(size_t n, size_t a) { return (n + a - 1) / a * a; }
 inline size_t padded_sites(int64_t V) { return round_up((size_t)V, 64); }
 
+// bytes per site of a spinor, and of the links and clover together
+constexpr size_t site_vec_bytes(int prec) { return prec == WCL_F64 ? 192 : prec == WCL_F32 ? 96 : 52; }
+constexpr size_t site_field_bytes(int prec) { return prec == WCL_F64 ? 960 : prec == WCL_F32 ? 480 : 244; }
 inline size_t spinor_rhs_bytes(int prec, int64_t V) {
     const size_t Vp = padded_sites(V);
     switch (prec) {

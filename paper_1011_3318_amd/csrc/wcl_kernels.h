@@ -21,17 +21,73 @@ int stage_to_host(int device, void* host, const void* dev, size_t bytes, hipStre
 void stage_ref();     // one per context: the staging memory is freed with the last
 void stage_unref();
 
-// order of the tiles in a launch, see walk_tile in wcl_device.h
+// Order in which a launch walks the tiles of a lattice field (or of a half
+// field) and the right-hand sides: rhs group, z range, part of the z range, t,
+// (x, y) column, tile, rhs of the group.
+//
+// Storage order runs a column through all of t before the next one.  When the
+// cross-section is cut in x or y too (extents such as 24: columns of 8 x 8 x 8),
+// the x and y neighbours outside the column are then a whole column away and
+// every one of them is fetched again after it left the L2; so the columns of
+// one z range are walked side by side.  On 24^3x48 that fetches 1.12 instead of
+// 1.37 GB per FP64 D-apply, 450 + 360 instead of 520 + 427 MB per FP32 Dhat.
 struct TileWalk {
-    int tiles;   // 64-site tiles of one column at one t; 0: storage order
+    int tiles;   // tiles of one column at one t; 0: storage order
+    int zt;      // of these, tiles walked together (divides tiles)
     int nxy;     // columns of one z range
     int Lt;
+    int group;   // right-hand sides walked together (the last group may have fewer)
 };
-// sites: sites per tile element (1: lattice fields, 2: half fields)
-inline TileWalk tile_walk(const Geom& g, int sites) {
-    const int nxy = g.nC[0] * g.nC[1];
-    if (nxy == 1 || g.S % (64 * sites) != 0) return TileWalk{0, 1, 1};
-    return TileWalk{g.S / (64 * sites), nxy, g.L[3]};
+
+__host__ __device__ inline int walk_tile(const TileWalk& k, int w) {
+    if (k.tiles == 0) return w;
+    const int nsub = k.tiles / k.zt;
+    int q = w / k.zt;
+    const int piece = w - q * k.zt;
+    const int cxy = q % k.nxy;
+    q /= k.nxy;
+    const int t = q % k.Lt;
+    q /= k.Lt;
+    const int sub = q % nsub, z = q / nsub;
+    return ((z * k.nxy + cxy) * k.Lt + t) * k.tiles + sub * k.zt + piece;
+}
+
+// Launch position lb of n walk positions times nrhs: the right-hand side, and
+// the walk position in *pos.
+__host__ __device__ inline int walk_rhs(const TileWalk& k, int lb, int n, int nrhs, int* pos) {
+    if (nrhs == 1) {
+        *pos = lb;
+        return 0;
+    }
+    const int g = lb / (n * k.group), rem = lb - g * (n * k.group);
+    const int left = nrhs - g * k.group, size = left < k.group ? left : k.group;
+    *pos = rem / size;
+    return g * k.group + rem - *pos * size;
+}
+
+// tile: sites per tile of the launch; sites: lattice sites per element of the
+// field (1: lattice fields, 2: half fields); vec, fields: bytes per element of
+// the vectors of one rhs and of the links and clover.
+//
+// What the t neighbours find in the 4 MB of an XCD's L2 is what one t slice of
+// the walk moves: above 3 MB its z range is halved as long as four planes
+// remain (below that the z neighbours at the ranges' ends cost more).
+// Right-hand sides go in groups of at most 6, each a walk of its own.
+// Measured, D-apply, whole ranges and groups / this rule: 32^4 FP32 131 / 126 us
+// (two planes: 150), FP64 285 / 278, 3 rhs FP32 298 / 282, FP64 631 / 590;
+// 16^3x32 with 12 rhs FP32 125 / 110 (groups of 4: 114, of 2: 129), FP64 263 / 247.
+// by_nrhs = false keeps the walk of the tiles the same for every nrhs, for
+// launches whose workgroups sum over several tiles.
+inline TileWalk tile_walk(const Geom& g, int tile, int sites, int nrhs, size_t vec, size_t fields, bool by_nrhs) {
+    const int groups = (nrhs + 5) / 6;
+    TileWalk k{0, 1, g.nC[0] * g.nC[1], g.L[3], (nrhs + groups - 1) / groups};
+    const int s = tile * sites;
+    if (g.S % s != 0) return k;
+    k.tiles = k.zt = g.S / s;
+    const size_t per_tile = (size_t)tile * k.nxy * ((by_nrhs ? k.group : 1) * vec + fields);
+    while (k.zt % 2 == 0 && k.zt * per_tile > (3u << 20) && k.zt / 2 * s >= 4 * g.c[0] * g.c[1]) k.zt /= 2;
+    if (k.nxy == 1 && k.zt == k.tiles) k.tiles = 0;   // that is storage order
+    return k;
 }
 
 struct DslashArgs {

@@ -73,6 +73,28 @@ def test_small_launches(W, dims):
     ctx.close()
 
 
+# groups of right-hand sides with a smaller last one (7 = 4 + 3, 13 = 5 + 5 + 3),
+# in the exchange layout (16x16x8x6: halved z ranges in FP64), with columns cut
+# in x (24x8x8x10) and in storage order (10x6x14x6); all above 4096 sites
+@pytest.mark.parametrize("dims", [(16, 16, 8, 6), (24, 8, 8, 10), (10, 6, 14, 6)])
+@pytest.mark.parametrize("nrhs", [7, 13])
+def test_rhs_groups(W, dims, nrhs):
+    ctx = W.Context(0)
+    lat = W.Lattice(ctx, dims, BC)
+    lat.upload_gauge(I.random_gauge(dims, 0.5, 1))
+    psi = I.gaussian_source(dims, 4, nrhs=nrhs)
+    for prec in (W.F64, W.F32, W.F16):
+        ops = [lat.apply_D] if prec == W.F16 else [lat.apply_D, lat.apply_schur]
+        x = lat.pack(psi, prec, nrhs)
+        for op in ops:
+            many = lat.unpack(op(prec, 0.126, 1.3, x, lat.empty(prec, nrhs), nrhs=nrhs), prec, nrhs)
+            for k in (0, 3, 4, 5, nrhs - 1):
+                one = op(prec, 0.126, 1.3, lat.pack(psi[k], prec), lat.empty(prec))
+                assert np.array_equal(lat.unpack(one, prec), many[k])
+    lat.close()
+    ctx.close()
+
+
 @pytest.mark.parametrize("dims", DIMS[:2])
 def test_schur_without_room_for_split_links(W, dims):
     """A budget that holds the call's own buffers but not the extra copy of
