@@ -756,7 +756,7 @@ struct SiteFields {
 #pragma unroll
         for (int k = 0; k < 72; ++k) c[k] = 0.f;
     }
-    WCL_DEV void load(const BlockArgs& a, int gi) {
+    WCL_DEV void load_links(const BlockArgs& a, int gi) {
         float t[18];
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
@@ -764,6 +764,8 @@ struct SiteFields {
 #pragma unroll
             for (int k = 0; k < 12; ++k) u[mu][k] = t[k];
         }
+    }
+    WCL_DEV void load_clover(const BlockArgs& a, int gi) {
         CloverIO<GP>::template load<false>(a.clover, a.g.V, gi, c);
     }
     template <int MU>
@@ -833,7 +835,7 @@ struct SiteFields<WCL_F16> {
     template <int MU>
     WCL_DEV float uk(int k) const { return (float)((k & 1) ? u[MU][k >> 1].y : u[MU][k >> 1].x); }
     WCL_DEV float ck_(int k) const { return (float)((k & 1) ? c[k >> 1].y : c[k >> 1].x); }
-    WCL_DEV void load(const BlockArgs& a, int gi) {
+    WCL_DEV void load_links(const BlockArgs& a, int gi) {
         const h4v* gp = (const h4v*)a.gauge;
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) {
@@ -852,6 +854,8 @@ struct SiteFields<WCL_F16> {
 #pragma unroll
             for (int k = 0; k < 6; ++k) r2[mu][k] = t[12 + k];
         }
+    }
+    WCL_DEV void load_clover(const BlockArgs& a, int gi) {
         const h8v* cp = (const h8v*)a.clover;
 #pragma unroll
         for (int g = 0; g < 9; ++g) {
@@ -1118,9 +1122,14 @@ struct FusedFields<WCL_F16, true> {
     using type = SiteFieldsDot;
 };
 
-// One crossing hop's data as stored: the neighbour's spinor (12 binary16 pairs
-// and its scale) and, for a backward hop, rows 0 and 1 of its link.
+// One crossing hop's data as stored: the neighbour's spinor (FP16: 12 binary16
+// pairs and a scale) and, for a backward hop, rows 0 and 1 of its link.
+template <int GP>
 struct CrossBuf {
+    float s[24], u[18];
+};
+template <>
+struct CrossBuf<WCL_F16> {
     h2v s[12];
     float sc;
     h2v u[6];
@@ -1128,18 +1137,23 @@ struct CrossBuf {
 
 // Requests the data of crossing hop K.  Every lane loads, lanes without the
 // hop at site 0: the loads stay outside divergent branches, so that the next
-// hop's are in flight while this one is computed.
-template <int K>
-WCL_DEV void cross_load(const BlockArgs& a, const char* vp, int n, CrossBuf& c) {
-    c.sc = load_spinor16(vp, a.g.V, n, c.s);
-    if constexpr (K % 2 == 1) {
-        const h4v* gp = (const h4v*)a.gauge;
+// hops' are in flight while this one is computed.
+template <int K, int GP>
+WCL_DEV void cross_load(const BlockArgs& a, const char* vp, int n, CrossBuf<GP>& c) {
+    if constexpr (GP == WCL_F16) {
+        c.sc = load_spinor16(vp, a.g.V, n, c.s);
+        if constexpr (K % 2 == 1) {
+            const h4v* gp = (const h4v*)a.gauge;
 #pragma unroll
-        for (int g = 0; g < 3; ++g) {
-            const h4v v = gp[tix(3 * (K / 2) + g, n, 12)];
-            c.u[2 * g] = h2v{v.x, v.y};
-            c.u[2 * g + 1] = h2v{v.z, v.w};
+            for (int g = 0; g < 3; ++g) {
+                const h4v v = gp[tix(3 * (K / 2) + g, n, 12)];
+                c.u[2 * g] = h2v{v.x, v.y};
+                c.u[2 * g + 1] = h2v{v.z, v.w};
+            }
         }
+    } else {
+        SpinorIO<GP>::load(vp, a.g.V, n, c.s);
+        if constexpr (K % 2 == 1) GaugeIO<GP>::template load_raw<false>(a.gauge, a.g.V, K / 2, n, c.u);
     }
 }
 
@@ -1182,18 +1196,24 @@ WCL_DEV void spin_project_scaled(const h2v s[12], float sc, float h[12]) {
     }
 }
 
-template <int K, bool DOT, typename FF>
-WCL_DEV void cross_hop(const FF& F, const CrossBuf& c, float mk, float ph, float acc[24]) {
+template <int K, int GP, bool DOT, typename FF>
+WCL_DEV void cross_hop(const FF& F, const CrossBuf<GP>& c, float mk, float ph, float acc[24]) {
     float h[12], w[12];
-    spin_project_scaled<K / 2, K % 2 == 0>(c.s, c.sc, h);
+    if constexpr (GP == WCL_F16) spin_project_scaled<K / 2, K % 2 == 0>(c.s, c.sc, h);
+    else spin_project<K / 2, K % 2 == 0>(c.s, h);
     if constexpr (K % 2 == 0) {
         F.template apply<K / 2, false>(h, w);
     } else {
         float u[18];
+        if constexpr (GP == WCL_F16) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            u[2 * k] = (float)c.u[k].x;
-            u[2 * k + 1] = (float)c.u[k].y;
+            for (int k = 0; k < 6; ++k) {
+                u[2 * k] = (float)c.u[k].x;
+                u[2 * k + 1] = (float)c.u[k].y;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) u[k] = c.u[k];
         }
         reconstruct_row2(u);
         su3_apply2<true>(u, h, w);
@@ -1202,14 +1222,25 @@ WCL_DEV void cross_hop(const FF& F, const CrossBuf& c, float mk, float ph, float
     spin_accumulate<K / 2, K % 2 == 0>(w, DOT && K % 2 == 0 ? mk : mk * ph, acc);
 }
 
-// rho -= the hops of D vprev that leave the domain (FP16 storage), two hops'
-// loads in flight.  Bound by the latency of those loads: with each hop's loads
-// inside its own divergent branch, a later sweep at 32^4 took 217 us (binary16
-// operands) and 272 us (FP32 arithmetic), pipelined 209 and 262; at 8^4 26.1
-// and 27.9, pipelined 25.2 and 26.4.
-template <bool DOT, typename FF>
-WCL_DEV void crossing_hops16(const BlockArgs& a, const FF& F, int rhs, int gi, const int x[4], bool active,
-                             const int nf[4], const int nb[4], float mk, float rho[24]) {
+// Hops K..7, D buffers: hop K is computed while the next D - 1 are in flight.
+template <int K, int D, int GP, bool DOT, typename FF>
+WCL_DEV void cross_chain(const BlockArgs& a, const FF& F, const char* vp, const int nbr[8], const bool cr[8], float mk,
+                         const float ph[8], CrossBuf<GP> (&c)[D], float acc[24]) {
+    if constexpr (K < 8) {
+        if (cr[K]) cross_hop<K, GP, DOT>(F, c[K % D], mk, ph[K], acc);
+        if constexpr (K + D < 8) cross_load<(K + D) & 7, GP>(a, vp, nbr[(K + D) & 7], c[K % D]);
+        cross_chain<K + 1, D, GP, DOT>(a, F, vp, nbr, cr, mk, ph, c, acc);
+    }
+}
+
+// rho -= the hops of D vprev that leave the domain.  Bound by the latency of
+// their loads: with each hop's loads inside its own divergent branch, a later
+// sweep at 32^4 took 217 us (binary16 operands), 272 us (FP16 storage, FP32
+// arithmetic) and 367 us (FP32), pipelined 209, 263 and 301; at 8^4 26.1, 27.9
+// and 27.9, pipelined 25.2, 26.5 and 25.7.
+template <int GP, bool DOT, typename FF>
+WCL_DEV void crossing_hops(const BlockArgs& a, const FF& F, int rhs, int gi, const int x[4], bool active,
+                           const int nf[4], const int nb[4], float mk, float rho[24]) {
     const char* vp = (const char*)a.vprev + rhs * a.vprev_stride;
     int nbr[8], lnk[8];
     float ph[8];
@@ -1223,14 +1254,12 @@ WCL_DEV void crossing_hops16(const BlockArgs& a, const FF& F, int rhs, int gi, c
     float acc[24];
 #pragma unroll
     for (int k = 0; k < 24; ++k) acc[k] = 0.f;
-    CrossBuf c0, c1;
-    cross_load<0>(a, vp, nbr[0], c0);
-#define WCL_XHOP(K, C, N)                                                       \
-    if constexpr ((K) < 7) cross_load<((K) + 1) & 7>(a, vp, nbr[((K) + 1) & 7], N); \
-    if (cr[K]) cross_hop<K, DOT>(F, C, mk, ph[K], acc);
-    WCL_XHOP(0, c0, c1) WCL_XHOP(1, c1, c0) WCL_XHOP(2, c0, c1) WCL_XHOP(3, c1, c0)
-    WCL_XHOP(4, c0, c1) WCL_XHOP(5, c1, c0) WCL_XHOP(6, c0, c1) WCL_XHOP(7, c1, c0)
-#undef WCL_XHOP
+    constexpr int D = !DOT && GP == WCL_F16 ? 3 : 2;   // what the registers hold
+    CrossBuf<GP> c[D];
+    cross_load<0, GP>(a, vp, nbr[0], c[0]);
+    cross_load<1, GP>(a, vp, nbr[1], c[1]);
+    if constexpr (D > 2) cross_load<2, GP>(a, vp, nbr[2], c[2]);
+    cross_chain<0, D, GP, DOT>(a, F, vp, nbr, cr, mk, ph, c, acc);
 #pragma unroll
     for (int k = 0; k < 24; ++k) rho[k] -= acc[k];
 }
@@ -1288,15 +1317,13 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
         block_site(a.g, a.B, blk, l, lc, x);
         gi = geom_index(a.g, x);
         SpinorIO<SRC>::load((const char*)a.src + rhs * a.src_stride, a.g.V, gi, rho);   // projection P r
+        F.load_links(a, gi);
         if constexpr (DOT) {
-            F.load_links(a, gi);
 #pragma unroll
             for (int mu = 0; mu < 4; ++mu)
                 if (a.g.bc[mu] < 0) F.negate_link(mu, x[mu] == a.g.L[mu] - 1);
-            if constexpr (RES == 1) F.load_clover(a, gi);
-        } else {
-            F.load(a, gi);
         }
+        if constexpr (RES == 1) F.load_clover(a, gi);
     }
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -1326,35 +1353,7 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
         // the domain, and v_{j-1} = x there, so r_j = r_{j-1} - D v_{j-1} is
         // the previous sweep's final rho minus the hops of D v_{j-1} that
         // leave the domain (Dirichlet D_Omega drops exactly those).
-        if constexpr (VP == WCL_F16) {
-            crossing_hops16<DOT>(a, F, rhs, gi, x, active, nf, nb, mk, rho);
-        } else if (active) {
-            const char* vp = (const char*)a.vprev + rhs * a.vprev_stride;
-            int nbr[8], lnk[8];
-            float ph[8];
-            hop_sites(a.g, gi, x, nbr, lnk, ph);
-            float acc[24];
-#pragma unroll
-            for (int k = 0; k < 24; ++k) acc[k] = 0.f;
-#define WCL_XHOP(K)                                                                       \
-    if (((K) % 2 == 0 ? nf[(K) / 2] : nb[(K) / 2]) < 0) {                                 \
-        float s[24], h[12], w[12], u[18];                                                 \
-        SpinorIO<VP>::load(vp, a.g.V, nbr[K], s);                                         \
-        spin_project<(K) / 2, (K) % 2 == 0>(s, h);                                        \
-        if ((K) % 2 == 0) {                                                               \
-            F.template apply<(K) / 2, false>(h, w);                                       \
-            if (DOT) ph[K] = 1.f; /* in the link */                                       \
-        } else {                                                                          \
-            GaugeIO<GP>::template load<false>(a.gauge, a.g.V, (K) / 2, lnk[K], u);        \
-            su3_apply2<true>(u, h, w);                                                    \
-        }                                                                                 \
-        spin_accumulate<(K) / 2, (K) % 2 == 0>(w, mk * ph[K], acc);                       \
-    }
-            WCL_XHOP(0) WCL_XHOP(1) WCL_XHOP(2) WCL_XHOP(3) WCL_XHOP(4) WCL_XHOP(5) WCL_XHOP(6) WCL_XHOP(7)
-#undef WCL_XHOP
-#pragma unroll
-            for (int k = 0; k < 24; ++k) rho[k] -= acc[k];
-        }
+        crossing_hops<GP, DOT>(a, F, rhs, gi, x, active, nf, nb, mk, rho);
     }
     if constexpr (RES == 1) {
         // The residual update of the previous sweep (Algorithm 1), fused:
@@ -1394,9 +1393,9 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
                 SpinorIO<VP>::store((char*)a.rout + rhs * a.rout_stride, a.g.V, gi, rho);
         }
     }
-    if constexpr (DOT && RES != 1) {
+    if constexpr (RES != 1) {
         // not before: the residual update needs the registers
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (DOT || RES == 2) __builtin_amdgcn_sched_barrier(0);
         if (active) F.load_clover(a, gi);
     }
     // binary16 operands: scale the domain's rho by 2^-e, 2^e near its RMS
