@@ -170,7 +170,7 @@ struct M3d {
 
 __device__ M3d load_link64(const Geom& g, const void* g64, const int x[4], int mu) {
     M3d A;
-    GaugeIO<WCL_F64>::load(g64, g.V, mu, geom_index(g, x), A.m);
+    GaugeIO<WCL_F64>::load<false>(g64, g.V, mu, geom_index(g, x), A.m);
     return A;
 }
 
@@ -178,9 +178,12 @@ __device__ M3d load_link64(const Geom& g, const void* g64, const int x[4], int m
 template <bool DAGB>
 __device__ M3d m3_mul(const M3d& A, const M3d& B) {
     M3d C;
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
         for (int j = 0; j < 3; ++j) {
             double re = 0, im = 0;
+#pragma unroll
             for (int k = 0; k < 3; ++k) {
                 double ar = A.m[2 * (3 * i + k)], ai = A.m[2 * (3 * i + k) + 1];
                 double br, bi;
@@ -202,7 +205,9 @@ __device__ M3d m3_mul(const M3d& A, const M3d& B) {
 
 __device__ M3d m3_dag(const M3d& A) {
     M3d C;
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
         for (int j = 0; j < 3; ++j) {
             C.m[2 * (3 * i + j)] = A.m[2 * (3 * j + i)];
             C.m[2 * (3 * i + j) + 1] = -A.m[2 * (3 * j + i) + 1];
@@ -210,10 +215,13 @@ __device__ M3d m3_dag(const M3d& A) {
     return C;
 }
 
+// mu and nu are uniform over the wavefront: compare and select, no indexing
 __device__ void shifted(const Geom& g, const int x[4], int mu, int dm, int nu, int dn, int y[4]) {
-    for (int k = 0; k < 4; ++k) y[k] = x[k];
-    y[mu] = (y[mu] + dm + g.L[mu]) % g.L[mu];
-    if (dn) y[nu] = (y[nu] + dn + g.L[nu]) % g.L[nu];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int v = x[k] + (k == mu ? dm : 0) + (k == nu ? dn : 0);
+        y[k] = v < 0 ? v + g.L[k] : v >= g.L[k] ? v - g.L[k] : v;
+    }
 }
 
 // Fhat_{mu nu}(x) = (1/8)[(Q - Q^dag) - 1/3 Tr(Q - Q^dag)], Q = sum of the
@@ -244,18 +252,23 @@ __device__ M3d fhat(const Geom& g, const void* g64, const int x[4], int mu, int 
     M3d L4 = m3_mul<true>(
         m3_mul<false>(m3_mul<false>(m3_dag(Unmn), load_link64(g, g64, xmn, mu)), load_link64(g, g64, xpmmn, nu)),
         Umx);
+#pragma unroll
     for (int k = 0; k < 18; ++k) Q.m[k] += L2.m[k] + L3.m[k] + L4.m[k];
     M3d F;
+#pragma unroll
     for (int i = 0; i < 3; ++i)
+#pragma unroll
         for (int j = 0; j < 3; ++j) {
             F.m[2 * (3 * i + j)] = Q.m[2 * (3 * i + j)] - Q.m[2 * (3 * j + i)];
             F.m[2 * (3 * i + j) + 1] = Q.m[2 * (3 * i + j) + 1] + Q.m[2 * (3 * j + i) + 1];
         }
     double trr = (F.m[0] + F.m[8] + F.m[16]) / 3.0, tri = (F.m[1] + F.m[9] + F.m[17]) / 3.0;
+#pragma unroll
     for (int i = 0; i < 3; ++i) {
         F.m[2 * (4 * i)] -= trr;
         F.m[2 * (4 * i) + 1] -= tri;
     }
+#pragma unroll
     for (int k = 0; k < 18; ++k) F.m[k] *= 0.125;
     return F;
 }
@@ -265,7 +278,9 @@ __device__ M3d fhat(const Geom& g, const void* g64, const int x[4], int mu, int 
 // packed as 6 real diagonal entries + 15 complex upper entries.
 __device__ void pack_block(const M3d& A3, const M3d& A1, const M3d& A2, double out[36]) {
     double M[6][6][2];
+#pragma unroll
     for (int a = 0; a < 3; ++a)
+#pragma unroll
         for (int b = 0; b < 3; ++b) {
             int k = 2 * (3 * a + b);
             double a3r = A3.m[k], a3i = A3.m[k + 1], a1r = A1.m[k], a1i = A1.m[k + 1], a2r = A2.m[k], a2i = A2.m[k + 1];
@@ -279,9 +294,12 @@ __device__ void pack_block(const M3d& A3, const M3d& A1, const M3d& A2, double o
             M[3 + a][3 + b][0] = a3i;
             M[3 + a][3 + b][1] = -a3r;
         }
+#pragma unroll
     for (int a = 0; a < 6; ++a) out[a] = M[a][a][0];
     int k = 0;
+#pragma unroll
     for (int a = 0; a < 6; ++a)
+#pragma unroll
         for (int b = a + 1; b < 6; ++b, ++k) {
             out[6 + 2 * k] = M[a][b][0];
             out[6 + 2 * k + 1] = M[a][b][1];
@@ -304,34 +322,91 @@ __device__ void store_clover_site(int V, int i, const double c[72], void* c64, v
     sc[i] = (float)m;
 }
 
-__global__ __launch_bounds__(128) void k_clover_build(Geom g, const void* g64, void* c64, void* c32, void* c16) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.V) return;
-    int x[4];
-    geom_coords(g, i, x);
-    M3d F01 = fhat(g, g64, x, 0, 1), F02 = fhat(g, g64, x, 0, 2), F03 = fhat(g, g64, x, 0, 3);
-    M3d F12 = fhat(g, g64, x, 1, 2), F13 = fhat(g, g64, x, 1, 3), F23 = fhat(g, g64, x, 2, 3);
-    M3d A3, A1, A2;
-    double c[72];
-    // spins 0,1:  sum sigma F = s3(-F_xy - F_zt) + s1(-F_xt - F_yz) + s2(F_xz - F_yt)
-    for (int k = 0; k < 18; ++k) {
-        A3.m[k] = -F01.m[k] - F23.m[k];
-        A1.m[k] = -F03.m[k] - F12.m[k];
-        A2.m[k] = F02.m[k] - F13.m[k];
+// One chiral block (bk) of a site's clover, m = the largest |entry| of both.
+__device__ void store_clover_block(int V, int i, int bk, const double c[36], double m, void* c64, void* c32, void* c16) {
+#pragma unroll
+    for (int k = 0; k < 18; ++k) ((d2v*)c64)[tix(18 * bk + k, i, 36)] = d2v{c[2 * k], c[2 * k + 1]};
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+        ((f4v*)c32)[tix(9 * bk + k, i, 18)] =
+            f4v{(float)c[4 * k], (float)c[4 * k + 1], (float)c[4 * k + 2], (float)c[4 * k + 3]};
+    const double inv = m > 0 ? 1.0 / m : 0.0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {   // 4 halves: half of a 16-byte element
+        h4v hv;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hv[j] = (_Float16)(float)(c[4 * k + j] * inv);
+        const int q = 9 * bk + k;
+        ((h4v*)c16)[2 * tix(q >> 1, i, 9) + (q & 1)] = hv;
     }
-    pack_block(A3, A1, A2, c);
-    // spins 2,3:  s3(-F_xy + F_zt) + s1(F_xt - F_yz) + s2(F_xz + F_yt)
-    for (int k = 0; k < 18; ++k) {
-        A3.m[k] = -F01.m[k] + F23.m[k];
-        A1.m[k] = F03.m[k] - F12.m[k];
-        A2.m[k] = F02.m[k] + F13.m[k];
+    if (bk == 0) ((float*)((char*)c16 + half_clover_scale_offset(V)))[i] = (float)m;
+}
+
+// 64 sites per workgroup, one wavefront per plane (mu, nu): each forms its
+// Fhat, which is anti-Hermitian (9 reals), and two of them build the two chiral
+// blocks from the six.  One thread per site with all six planes needed 512
+// registers and spilled 124 of them: 16^3x32 193 -> 146 us, 24^3x48 1107 -> 762.
+// What is left is the 96 links a site's leaves read (9 KB a site from the L2);
+// fewer registers (one leaf's links at a time, three waves per SIMD): 144 us.
+__global__ __launch_bounds__(384) void k_clover_build(Geom g, const void* g64, void* c64, void* c32, void* c16) {
+    __shared__ double sf[6][9][64];
+    __shared__ double smax[2][64];
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int i = blockIdx.x * 64 + l;
+    const bool active = i < g.V;
+    if (active) {
+        int x[4];
+        geom_coords(g, i, x);
+        // planes (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+        const int mu = p < 3 ? 0 : p < 5 ? 1 : 2, nu = p < 3 ? p + 1 : p < 5 ? p - 1 : 3;
+        const M3d F = fhat(g, g64, x, mu, nu);
+        // diagonal (imaginary), then (0,1), (0,2), (1,2)
+        const double v[9] = {F.m[1], F.m[9], F.m[17], F.m[2], F.m[3], F.m[4], F.m[5], F.m[10], F.m[11]};
+#pragma unroll
+        for (int k = 0; k < 9; ++k) sf[p][k][l] = v[k];
     }
-    pack_block(A3, A1, A2, c + 36);
-    store_clover_site(g.V, i, c, c64, c32, c16);
+    __syncthreads();
+    double c[36];
+    if (p < 2 && active) {
+        // p = 0, spins 0,1:  sum sigma F = s3(-F_xy - F_zt) + s1(-F_xt - F_yz) + s2(F_xz - F_yt)
+        // p = 1, spins 2,3:  s3(-F_xy + F_zt) + s1(F_xt - F_yz) + s2(F_xz + F_yt)
+        const double sg = p ? 1.0 : -1.0;
+        M3d A[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            double v[9];
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+                v[k] = q == 0   ? sg * sf[5][k][l] - sf[0][k][l]
+                       : q == 1 ? sg * sf[2][k][l] - sf[3][k][l]
+                                : sf[1][k][l] + sg * sf[4][k][l];
+            double* m = A[q].m;
+            m[0] = m[8] = m[16] = 0.0;
+            m[1] = v[0];
+            m[9] = v[1];
+            m[17] = v[2];
+            m[2] = v[3];
+            m[6] = -v[3];
+            m[3] = m[7] = v[4];
+            m[4] = v[5];
+            m[12] = -v[5];
+            m[5] = m[13] = v[6];
+            m[10] = v[7];
+            m[14] = -v[7];
+            m[11] = m[15] = v[8];
+        }
+        pack_block(A[0], A[1], A[2], c);
+        double m = 0;
+#pragma unroll
+        for (int k = 0; k < 36; ++k) m = fmax(m, fabs(c[k]));
+        smax[p][l] = m;
+    }
+    __syncthreads();
+    if (p < 2 && active) store_clover_block(g.V, i, p, c, fmax(smax[0][l], smax[1][l]), c64, c32, c16);
 }
 
 int launch_clover_build(const Geom& g, const void* g64, void* c64, void* c32, void* c16, hipStream_t st) {
-    k_clover_build<<<(g.V + 127) / 128, 128, 0, st>>>(g, g64, c64, c32, c16);
+    k_clover_build<<<(g.V + 63) / 64, 384, 0, st>>>(g, g64, c64, c32, c16);
     WCL_HIP(hipGetLastError());
     return WCL_OK;
 }
