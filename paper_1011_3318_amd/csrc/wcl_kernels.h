@@ -239,8 +239,10 @@ struct BlockArgs {
 };
 
 int launch_blk_project(const BlockArgs& a, int src_prec, int bicgstab, hipStream_t st);
-int launch_blk_dslash(const BlockArgs& a, int gp, hipStream_t st);
-int launch_blk_update(const BlockArgs& a, int vj_prec, int last, hipStream_t st);
+// src: -1, or the precision of the projection source that the first MR step
+// reads in place of rho in the workspace
+int launch_blk_dslash(const BlockArgs& a, int gp, int src, hipStream_t st);
+int launch_blk_update(const BlockArgs& a, int vj_prec, int src, int last, hipStream_t st);
 // block Jacobi step: x = x + A^{-1} (b - q) (first: x = A^{-1} b), b = rho
 int launch_blk_jacobi(const BlockArgs& a, int gp, int vj_prec, int first, int last, hipStream_t st);
 // truncated BiCGStab: p update, s update, x/r update (see wcl_block.hip)

@@ -447,17 +447,17 @@ static int split_domain_solve(const BlockArgs& a0, const Blocks& B, int storage,
     BlockArgs a = a0;
     const int n = B.n_dominv;
     if (B.solver == WCL_DOMSOLVE_MR) {
-        WCL_CHECK(launch_blk_project(a, src_prec, 0, st));
         for (int k = 0; k < n; ++k) {
-            WCL_CHECK(launch_blk_dslash(a, storage, st));
-            WCL_CHECK(launch_blk_update(a, storage, k == n - 1, st));
+            const int src = k == 0 ? src_prec : -1;
+            WCL_CHECK(launch_blk_dslash(a, storage, src, st));
+            WCL_CHECK(launch_blk_update(a, storage, src, k == n - 1, st));
         }
     } else if (B.solver == WCL_DOMSOLVE_JACOBI) {
         WCL_CHECK(launch_blk_project(a, src_prec, 0, st));
         BlockArgs ax = a;   // q = D_{Omega'} x
         ax.rho = bf.x;
         for (int k = 0; k < n; ++k) {
-            if (k > 0) WCL_CHECK(launch_blk_dslash(ax, storage, st));
+            if (k > 0) WCL_CHECK(launch_blk_dslash(ax, storage, -1, st));
             WCL_CHECK(launch_blk_jacobi(a, storage, storage, k == 0, k == n - 1, st));
         }
     } else {
@@ -472,9 +472,9 @@ static int split_domain_solve(const BlockArgs& a0, const Blocks& B, int storage,
         at.partial = bf.bpart[2];
         for (int k = 0; k < n; ++k) {
             WCL_CHECK(launch_bcg_p(a, k, st));
-            WCL_CHECK(launch_blk_dslash(av, storage, st));
+            WCL_CHECK(launch_blk_dslash(av, storage, -1, st));
             WCL_CHECK(launch_bcg_s(a, st));
-            WCL_CHECK(launch_blk_dslash(at, storage, st));
+            WCL_CHECK(launch_blk_dslash(at, storage, -1, st));
             WCL_CHECK(launch_bcg_xr(a, storage, k == n - 1, st));
         }
     }
@@ -1332,7 +1332,7 @@ int wcl_apply_D_blocks(wcl_lattice* lat, const wcl_ras_params* ras, double kappa
     const size_t ob = (size_t)a.NE * 24 * sizeof(double);
     WCL_CHECK(ws->get("blocks.out", ob, &stage));
     WCL_CHECK(launch_blk_project(a, WCL_F32, 0, st));
-    WCL_CHECK(launch_blk_dslash(a, ras->storage, st));
+    WCL_CHECK(launch_blk_dslash(a, ras->storage, -1, st));
     WCL_CHECK(launch_blk_unpack(a, (const float*)a.q, (double*)stage, st));
     WCL_HIP(hipMemcpyAsync(out_host, stage, ob, hipMemcpyDeviceToHost, st));
     WCL_HIP(hipStreamSynchronize(st));
