@@ -68,3 +68,28 @@ def test_many_threads_and_contexts(W):
     for t in th:
         t.join()
     assert bad == []
+
+
+def test_kept_staging_gives_way(W):
+    """The device block kept between transfers is not counted as in use and is
+    given back when another allocation needs its room: a budget of exactly two
+    resident lattices and one upload's staging is enough, as without it."""
+    dims = (8, 8, 8, 8)
+    V = I.volume(dims)
+    # links 384 + 192 + 96, clover 576 + 288 + 148 bytes a site; staged FP64 links
+    resident, staged = 1684 * V, 576 * V
+    ctx = W.Context(0, hbm_budget=2 * resident + staged)
+    U = I.random_gauge(dims, 0.5, 1)
+    lats = []
+    for k in range(2):
+        lat = W.Lattice(ctx, dims)
+        lat.upload_gauge(U)
+        psi = I.gaussian_source(dims, 3 + k)
+        assert np.array_equal(lat.unpack(lat.pack(psi, W.F64), W.F64), psi)
+        lats.append(lat)
+        assert ctx.bytes_in_use() <= (k + 1) * resident
+    lats[0].upload_gauge(U)   # again, into the resident fields
+    for lat in lats:
+        lat.close()
+    assert ctx.bytes_in_use() == 0
+    ctx.close()
