@@ -1343,15 +1343,24 @@ WCL_DEV void crossing_hops(const BlockArgs& a, const FF& F, int rhs, int gi, con
 // update: 162-167 VGPRs, no spill (193 before).  First / later sweep of 4 steps
 // at 32^4: 195 / 248 -> 172 / 209 us; NRAS 5: 1183 -> 1021 us.  RES == 1 (overlap)
 // needs the clover during its residual update and keeps two.
-template <bool DOT, int RES>
+//
+// FEW: a grid that cannot fill the third place (at most two domains per CU)
+// keeps the whole solution in registers (191-197 VGPRs) and spares each step
+// the LDS passes: first / later sweep of 4 steps, three per CU -> FEW, 8^4
+// (16 domains) 20.8 / 25.2 -> 19.3 / 24.2 us, 16^3x32 (512) 31.5 / 36.7 ->
+// 30.0 / 35.8; with 768 domains two per CU take 43.1 / 54.8, three 39.5 / 47.9.
+// The operations and their order are the same, so the bits are.
+template <bool DOT, int RES, bool FEW>
 struct FusedShape {
-    static constexpr int xl = DOT ? 16 : 0;   // components of the solution kept in LDS
+    static constexpr int xl = DOT && !FEW ? 16 : 0;   // components of the solution kept in LDS
     static constexpr int lds_words = DOT ? 36 + xl : 72;
-    static constexpr int min_waves = DOT && RES != 1 ? 3 : WCL_FUSED_MINWAVES;
+    static constexpr int min_waves = DOT && RES != 1 && !FEW ? 3 : WCL_FUSED_MINWAVES;
+    // with registers to spare the clover's loads start with the others
+    static constexpr bool clover_first = RES == 1 || (RES == 0 && (!DOT || FEW));
 };
 
-template <int GP, int SRC, int VP, int NT, int RES, bool DOT>
-__global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_fused(BlockArgs a, int write_vj) {
+template <int GP, int SRC, int VP, int NT, int RES, bool DOT, bool FEW>
+__global__ __launch_bounds__(NT, (FusedShape<DOT, RES, FEW>::min_waves)) void k_blk_fused(BlockArgs a, int write_vj) {
     extern __shared__ float lds[];
     float* s_rho = lds;                 // [24][NT]
     float* s_bwd = lds + 24 * NT;       // [4][12][NT] FP32, or [4][6][NT] binary16 pairs (DOT)
@@ -1383,7 +1392,7 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
             for (int mu = 0; mu < 4; ++mu)
                 if (a.g.bc[mu] < 0) F.negate_link(mu, x[mu] == a.g.L[mu] - 1);
         }
-        if constexpr (RES == 1) F.load_clover(a, gi);
+        if constexpr (FusedShape<DOT, RES, FEW>::clover_first) F.load_clover(a, gi);
     }
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu) {
@@ -1453,9 +1462,9 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
                 SpinorIO<VP>::store((char*)a.rout + rhs * a.rout_stride, a.g.V, gi, rho);
         }
     }
-    if constexpr (RES != 1) {
+    if constexpr (!FusedShape<DOT, RES, FEW>::clover_first) {
         // not before: the residual update needs the registers
-        if constexpr (DOT || RES == 2) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
         if (active) F.load_clover(a, gi);
     }
     // binary16 operands: scale the domain's rho by 2^-e, 2^e near its RMS
@@ -1485,7 +1494,7 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
         // own rho in registers (FP32); the neighbours read its binary16 pairs
         h2v* s_rp = (h2v*)lds;               // [12][NT]
         h2v* s_bw = (h2v*)(lds + 12 * NT);   // [4][6][NT]
-        constexpr int XL = FusedShape<DOT, RES>::xl;
+        constexpr int XL = FusedShape<DOT, RES, FEW>::xl;
         f4v* s_xs = (f4v*)(lds + 36 * NT);   // [XL / 4][NT]
 #pragma unroll
         for (int g = 0; g < XL / 4; ++g) s_xs[g * NT + l] = f4v{0.f, 0.f, 0.f, 0.f};
@@ -1501,7 +1510,7 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
         }
         for (int step = 0; step < a.B.n_dominv; ++step) {
             F.refresh();
-            asm volatile("" : "+v"(nbrs[0]), "+v"(nbrs[1]), "+v"(have));
+            if constexpr (XL > 0) asm volatile("" : "+v"(nbrs[0]), "+v"(nbrs[1]), "+v"(have));
             h2v rp[12];
 #pragma unroll
             for (int k = 0; k < 12; ++k) {
@@ -1752,14 +1761,17 @@ __global__ __launch_bounds__(NT, (FusedShape<DOT, RES>::min_waves)) void k_blk_f
 
 int fused_threads(int ev) { return ev <= 256 ? 256 : 0; }
 
-template <int GP, int SRC, int VP, int NT, int RES, bool DOT>
+template <int GP, int SRC, int VP, int NT, int RES, bool DOT, bool FEW = false>
 static int launch_fused_t(const BlockArgs& a, hipStream_t st) {
-    const size_t lds = (size_t)FusedShape<DOT, RES>::lds_words * NT * sizeof(float);
+    // up to two domains for each of the 256 CUs: a third place stays empty
+    if constexpr (DOT && !FEW && RES != 1)
+        if ((int64_t)a.B.nblocks * a.nrhs <= 512) return launch_fused_t<GP, SRC, VP, NT, RES, DOT, true>(a, st);
+    const size_t lds = (size_t)FusedShape<DOT, RES, FEW>::lds_words * NT * sizeof(float);
     // dynamic LDS above the 64 KB default; set once per instantiation (thread-safe static)
-    static const hipError_t attr = hipFuncSetAttribute((const void*)k_blk_fused<GP, SRC, VP, NT, RES, DOT>,
+    static const hipError_t attr = hipFuncSetAttribute((const void*)k_blk_fused<GP, SRC, VP, NT, RES, DOT, FEW>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     WCL_HIP(attr);
-    k_blk_fused<GP, SRC, VP, NT, RES, DOT><<<a.B.nblocks * a.nrhs, NT, lds, st>>>(a, a.vj != nullptr);
+    k_blk_fused<GP, SRC, VP, NT, RES, DOT, FEW><<<a.B.nblocks * a.nrhs, NT, lds, st>>>(a, a.vj != nullptr);
     WCL_HIP(hipGetLastError());
     return WCL_OK;
 }

@@ -104,7 +104,8 @@ WCL_DEV void eo_site(const EoArgs& a, int h, const T z[24], T y[24]) {
 // Bound by HBM.  Fields and links come from parity-split copies: with the
 // full-lattice ones each line of the clover and of the forward links is half
 // unused.  Dhat in FP32 on 24^3x48 (apply_schur; 541 MB at least): 271 us in
-// five launches from the full fields, 156 us in two from the split ones.
+// five launches from the full fields, 156 us in two from the split ones (163
+// with several configurations in rotation, when nothing stays in a cache).
 template <int P, int MODE, int EPI, bool SL, bool FULL, bool NT, bool LINK_NT>
 __global__ __launch_bounds__(256, P == WCL_F64 ? 2 : 4) void k_eo(EoArgs a) {
     using T = typename Real<P>::T;

@@ -75,7 +75,7 @@ int launch_unpack_spinor(const Geom& g, int prec, int nrhs, const void* soa, siz
 //
 // Bound by the read of the links (144 B each).  On one host thread the test
 // took 33 ms for 16^3x32 (524 288 links); with it here an upload, the clover
-// build and one FP64 D-apply take 3.2 instead of 35.5 ms.
+// build and one FP64 D-apply take 2.1 instead of 35.4 ms.
 __global__ __launch_bounds__(256) void k_check_links(int64_t n, const double* __restrict__ aos, double bound, int* bad) {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;

@@ -11,7 +11,8 @@
 //
 // Measured: pack + unpack of a 25 MB FP64 source (16^3x32) 2.94 -> 1.75 ms
 // (0.47 ms each way at the pinned rate of 54 GB/s), the upload of 75 MB of
-// links with the clover build and a D-apply 3.19 -> 2.33 ms.  Threads x chunk:
+// links with the clover build and a D-apply 3.19 -> 2.33 ms (2.1 with the
+// clover build of today and the device block kept).  Threads x chunk:
 // 4 x 1 MiB 1.96 / 2.96 ms, 8 x 1 MiB 2.42 / 3.01, 4 x 2 MiB 1.74 / 2.48,
 // 3 x 4 MiB 1.72 / 2.30, 2 x 4 MiB 1.75 / 2.33: each chunk's copy and event
 // cost more than the overlap of smaller ones gains.

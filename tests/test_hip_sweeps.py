@@ -2,7 +2,8 @@
 projection source in place (one step only, where it is also the last; ragged
 domains; several right-hand sides), and the residual update's crossing hops of
 the on-chip path on domains with a side of one site, antiperiodic directions and
-right-hand sides in one launch."""
+right-hand sides in one launch; the binary16-operand sweeps on either side of the
+grid size above which three domains share a CU."""
 import numpy as np
 import pytest
 
@@ -70,5 +71,32 @@ def test_crossing_hops(W, dims, block, bc, storage, arith, tol):
         assert rel_err(got[k], o.ras(r[k], KAPPA, CSW, block, 0, 3, 3)) <= tol
     one = lat.unpack(lat.ras_precondition(ras, KAPPA, CSW, lat.pack(r[1], W.F32), lat.empty(W.F32)), W.F32)
     assert np.array_equal(one, got[1])
+    lat.close()
+    ctx.close()
+
+
+# 256 domains per right-hand side: 256 and 512 workgroups run the form with two
+# domains per CU, 768 the one with three; the bits must not depend on it
+@pytest.mark.parametrize("n_ras,nd", [(1, 1), (2, 4), (3, 3)])
+@pytest.mark.parametrize("bc", [(1, 1, 1, 1), (-1, 1, 1, -1)])
+def test_domains_per_cu(W, bc, n_ras, nd):
+    dims, block = (8, 8, 8, 8), (2, 2, 2, 2)
+    ctx = W.Context(0)
+    U = I.random_gauge(dims, 0.5, 1)
+    lat = W.Lattice(ctx, dims, bc)
+    lat.upload_gauge(U)
+    r = I.gaussian_source(dims, 6, nrhs=3)
+    ras = W.RasParams.make(block=block, s=0, n_ras=n_ras, n_dominv=nd, storage=W.F16, arith=W.ARITH_DOT2)
+
+    def run(v, n):
+        return lat.unpack(lat.ras_precondition(ras, KAPPA, CSW, lat.pack(v, W.F32, n), lat.empty(W.F32, n), nrhs=n),
+                          W.F32, n)
+
+    three = run(r, 3)
+    assert np.array_equal(run(r[:2], 2), three[:2])
+    for k in range(3):
+        assert np.array_equal(np.asarray(run(r[k:k + 1], 1)).reshape(three[k].shape), three[k])
+    o = Oracle(dims, U, bc=bc)
+    assert rel_err(three[1], o.ras(r[1], KAPPA, CSW, block, 0, n_ras, nd)) <= 2e-2
     lat.close()
     ctx.close()
