@@ -439,6 +439,23 @@ static void tl_mark(Timeline* tl, int cat) {
     if (tl) tl->mark(cat);
 }
 
+// Whether the first MR step of the split path reads the projection's source in
+// place (no k_blk_project pass, nothing of the workspace read) or from a copy
+// in domain order.  In place every site's eight neighbours come from the
+// lattice in pieces as long as a domain's x side, once more for each domain
+// that holds them.  Without overlap that pays unless a domain is so large that
+// its t neighbours leave the L2 (FP32, 2 sweeps of 2 steps, copy / in place:
+// 32^4, 8^3x16 1.32 / 1.19 ms, 16^4 1.66 / 1.57, but 4x32^3 2.47 / 2.56).  With
+// overlap it pays for rows of eight sites and more out of a source that the
+// L2s hold (32 MB): 16^3x32, 8^4 + 1 0.35 / 0.30 ms, 8^4 + 2 0.83 / 0.72,
+// 8^3x16 + 1 0.41 / 0.40, but 4x8^2x16 + 1 0.61 / 0.65, 4^2x8^2 + 1 0.73 /
+// 0.76; 32^4, 8^3x16 + 1 3.87 / 4.18.  The results are the same bit for bit.
+static bool split_reads_source(const Geom& g, const Blocks& B) {
+    const bool overlap = B.s[0] || B.s[1] || B.s[2] || B.s[3];
+    if (!overlap) return B.ev <= 65536;
+    return B.e[0] >= 8 && spinor_rhs_bytes(WCL_F32, g.V) <= (32u << 20);
+}
+
 // One domain solve on the split path for the current pass: projection of
 // the source, the domain solver's iterations, and the write-out (restriction
 // to the owned sites, or the additive gather).
@@ -447,8 +464,10 @@ static int split_domain_solve(const BlockArgs& a0, const Blocks& B, int storage,
     BlockArgs a = a0;
     const int n = B.n_dominv;
     if (B.solver == WCL_DOMSOLVE_MR) {
+        const bool in_place = split_reads_source(a.g, B);
+        if (!in_place) WCL_CHECK(launch_blk_project(a, src_prec, 0, st));
         for (int k = 0; k < n; ++k) {
-            const int src = k == 0 ? src_prec : -1;
+            const int src = k == 0 && in_place ? src_prec : -1;
             WCL_CHECK(launch_blk_dslash(a, storage, src, st));
             WCL_CHECK(launch_blk_update(a, storage, src, k == n - 1, st));
         }

@@ -24,7 +24,10 @@ def W():
 
 # (dims, block, s): 384 extended sites (a half-empty second workgroup), 1296
 # (16 sites in the last one), one domain spanning the whole lattice
-SPLIT = [((8, 4, 6, 4), (4, 2, 2, 4), 1), ((8, 8, 8, 8), (4, 4, 4, 4), 1), ((4, 6, 4, 4), (4, 6, 4, 4), 0)]
+# (these overlapping ones copy the source first, their x side being short), and
+# two overlapping ones that read it in place
+SPLIT = [((8, 4, 6, 4), (4, 2, 2, 4), 1), ((8, 8, 8, 8), (4, 4, 4, 4), 1), ((4, 6, 4, 4), (4, 6, 4, 4), 0),
+         ((16, 4, 4, 4), (8, 4, 4, 4), 1), ((12, 4, 6, 8), (6, 4, 3, 4), 1)]
 
 
 # the tolerances of the preconditioner's own tests: FP32 1e-4, FP16 storage 2e-2
