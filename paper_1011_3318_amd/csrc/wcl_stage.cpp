@@ -126,7 +126,11 @@ int copy(int device, void* dev, void* host, size_t bytes, hipStream_t st) {
         if (!TO_DEVICE) WCL_HIP(hipStreamSynchronize(st));
         return WCL_OK;
     }
-    const int T = std::max(1, std::min(kThreads, (int)std::thread::hardware_concurrency() / 2));
+    // hipStreamPerThread names another stream in every thread: only the caller's
+    // own is ordered with what it has queued there, so it does all the stripes
+    const int T = st == hipStreamPerThread
+                      ? 1
+                      : std::max(1, std::min(kThreads, (int)std::thread::hardware_concurrency() / 2));
     hipError_t err[kThreads];
     std::fill(err, err + kThreads, hipSuccess);
     std::thread th[kThreads];

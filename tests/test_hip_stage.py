@@ -93,3 +93,24 @@ def test_kept_staging_gives_way(W):
         lat.close()
     assert ctx.bytes_in_use() == 0
     ctx.close()
+
+
+def test_per_thread_stream(W):
+    """The per-thread default stream (handle 2), which names another stream in
+    every host thread: an unpack of several chunks behind queued work returns
+    that work's result."""
+    dims, per_thread = (16, 16, 12, 16), 2
+    ctx = W.Context(0)
+    lat = W.Lattice(ctx, dims)
+    lat.upload_gauge(I.random_gauge(dims, 0.5, 1))
+    psi = I.gaussian_source(dims, 4)
+    x, y = lat.pack(psi, W.F64), lat.zeros(W.F64)
+    for _ in range(100):   # a few ms
+        lat.apply_D(W.F64, 0.1, 1.0, x, y, stream=per_thread)
+    lat.apply_D(W.F64, 0.126, 1.0, x, y, stream=per_thread)
+    got = lat.unpack(y, W.F64, stream=per_thread)
+    z = lat.apply_D(W.F64, 0.126, 1.0, lat.pack(psi, W.F64, stream=per_thread), lat.zeros(W.F64))
+    torch.cuda.synchronize()
+    assert np.array_equal(got, lat.unpack(z, W.F64))
+    lat.close()
+    ctx.close()
