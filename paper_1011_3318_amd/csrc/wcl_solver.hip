@@ -74,22 +74,27 @@ struct Timeline {
 struct Workspace {
     wcl_ctx* ctx = nullptr;
     Timeline tl;
-    // key of the site-term inverse held in "ainv.*" (see site_inverse)
-    uint64_t ainv_uid = 0, ainv_gen = 0;
-    double ainv_kappa = 0.0, ainv_csw = 0.0;
-    const void* ainv_ptr = nullptr;
-    // keys of the even-odd fields held in "eo.ainv.*", "eo.clov.*" and
-    // "eo.links.*", one per precision (see eo_fields)
-    struct EoKey {
-        uint64_t uid = 0, gen = 0;
+    // What the fields kept in three buffers were built for.  A buffer is named
+    // by the number of its allocation: a new one of the same size may have the
+    // old one's address, but not its contents.
+    struct FieldKey {
+        uint64_t uid = 0, gen = 0;   // lattice and its clover field
         double kappa = 0.0, csw = 0.0;
-        const void *ainv = nullptr, *clov = nullptr, *links = nullptr;
-    } eo_key[2];
+        uint64_t buf[3] = {0, 0, 0};
+        bool operator==(const FieldKey& o) const {
+            return uid == o.uid && gen == o.gen && kappa == o.kappa && csw == o.csw && buf[0] == o.buf[0] &&
+                   buf[1] == o.buf[1] && buf[2] == o.buf[2];
+        }
+    };
+    FieldKey ainv_key;    // the site-term inverse in "ainv.*" (see site_inverse)
+    FieldKey eo_key[2];   // "eo.ainv.*", "eo.clov.*", "eo.links.*", one per precision (see eo_fields)
     struct Item {
         std::string name;
         void* p;
         size_t bytes;
+        uint64_t id;      // number of the allocation, never used again
     };
+    uint64_t last_id = 0;
     std::vector<Item> items;
     struct Pinned {
         std::string name;
@@ -98,26 +103,22 @@ struct Workspace {
     };
     std::vector<Pinned> pinned;   // host mirrors of the scalar arrays, one per solver level
 
-    int get(const std::string& name, size_t bytes, void** out) {
-        for (auto& it : items)
-            if (it.name == name) {
-                if (it.bytes >= bytes) {
-                    *out = it.p;
-                    return WCL_OK;
-                }
-                wcl_dev_free(ctx, it.p, it.bytes);
-                it.p = nullptr;
-                it.bytes = 0;
-                WCL_CHECK(wcl_dev_alloc(ctx, &it.p, bytes));
-                it.bytes = bytes;
-                *out = it.p;
-                return WCL_OK;
-            }
-        Item it{name, nullptr, 0};
-        WCL_CHECK(wcl_dev_alloc(ctx, &it.p, bytes));
-        it.bytes = bytes;
-        items.push_back(it);
+    // id (optional): the number of the buffer's allocation
+    int get(const std::string& name, size_t bytes, void** out, uint64_t* id = nullptr) {
+        size_t k = 0;
+        while (k < items.size() && items[k].name != name) ++k;
+        if (k == items.size()) items.push_back(Item{name, nullptr, 0, 0});
+        Item& it = items[k];
+        if (it.bytes < bytes) {
+            wcl_dev_free(ctx, it.p, it.bytes);
+            it.p = nullptr;
+            it.bytes = 0;
+            WCL_CHECK(wcl_dev_alloc(ctx, &it.p, bytes));
+            it.bytes = bytes;
+            it.id = ++last_id;
+        }
         *out = it.p;
+        if (id) *id = it.id;
         return WCL_OK;
     }
     bool has(const std::string& name, size_t bytes) const {
@@ -366,13 +367,12 @@ static void ras_buffer_list(const Blocks& B, bool fused, int storage, int64_t V,
 // until one of them changes.
 static int site_inverse(wcl_lattice* lat, Workspace* ws, double kappa, double csw, hipStream_t st, void* out[3]) {
     const int64_t V = lat->V;
-    WCL_CHECK(ws->get("ainv.f64", clover_bytes(WCL_F64, V), &out[0]));
-    WCL_CHECK(ws->get("ainv.f32", clover_bytes(WCL_F32, V), &out[1]));
-    WCL_CHECK(ws->get("ainv.f16", clover_bytes(WCL_F16, V), &out[2]));
-    if (ws->ainv_uid == lat->uid && ws->ainv_gen == lat->clover_gen && ws->ainv_kappa == kappa &&
-        ws->ainv_csw == csw && ws->ainv_ptr == out[0])
-        return WCL_OK;
-    ws->ainv_uid = 0;
+    Workspace::FieldKey key{lat->uid, lat->clover_gen, kappa, csw};
+    WCL_CHECK(ws->get("ainv.f64", clover_bytes(WCL_F64, V), &out[0], &key.buf[0]));
+    WCL_CHECK(ws->get("ainv.f32", clover_bytes(WCL_F32, V), &out[1], &key.buf[1]));
+    WCL_CHECK(ws->get("ainv.f16", clover_bytes(WCL_F16, V), &out[2], &key.buf[2]));
+    if (ws->ainv_key == key) return WCL_OK;
+    ws->ainv_key = Workspace::FieldKey{};
     int* bad = nullptr;
     WCL_CHECK(ws->get("ainv.bad", 256, (void**)&bad));
     int hbad = 0;
@@ -384,11 +384,7 @@ static int site_inverse(wcl_lattice* lat, Workspace* ws, double kappa, double cs
         wcl_set_error("the site term 1 + c_sw kappa C(x) is singular at some site (kappa %g, c_sw %g)", kappa, csw);
         return WCL_EINVAL;
     }
-    ws->ainv_uid = lat->uid;
-    ws->ainv_gen = lat->clover_gen;
-    ws->ainv_kappa = kappa;
-    ws->ainv_csw = csw;
-    ws->ainv_ptr = out[0];
+    ws->ainv_key = key;
     return WCL_OK;
 }
 
@@ -404,23 +400,24 @@ static int eo_fields(wcl_lattice* lat, Workspace* ws, double kappa, double csw, 
                      hipStream_t st, EoFields* f) {
     const int64_t Vh = lat->V / 2;
     const std::string tag = prec == WCL_F64 ? ".f64" : ".f32";
-    WCL_CHECK(ws->get("eo.ainv" + tag, clover_bytes(prec, Vh), &f->ainv));
-    WCL_CHECK(ws->get("eo.clov" + tag, clover_bytes(prec, Vh), &f->clov));
+    Workspace::FieldKey key{lat->uid, lat->clover_gen, kappa, csw};
+    WCL_CHECK(ws->get("eo.ainv" + tag, clover_bytes(prec, Vh), &f->ainv, &key.buf[0]));
+    WCL_CHECK(ws->get("eo.clov" + tag, clover_bytes(prec, Vh), &f->clov, &key.buf[1]));
     int* bad = nullptr;
     WCL_CHECK(ws->get("ainv.bad", 256, (void**)&bad));
     if (want_links) {
         const size_t bytes = 2 * gauge_bytes(prec, Vh), room = 16 * spinor_rhs_bytes(WCL_F64, lat->V);
         if (ws->has("eo.links" + tag, bytes) || wcl_dev_room(lat->ctx) >= bytes + room) {
-            const int rc = ws->get("eo.links" + tag, bytes, &f->links);
+            const int rc = ws->get("eo.links" + tag, bytes, &f->links, &key.buf[2]);
             if (rc == WCL_ENOMEM) f->links = nullptr;
             else WCL_CHECK(rc);
         }
     }
-    Workspace::EoKey& k = ws->eo_key[prec == WCL_F64 ? 0 : 1];
-    if (k.uid == lat->uid && k.gen == lat->clover_gen && k.kappa == kappa && k.csw == csw && k.ainv == f->ainv &&
-        k.clov == f->clov && (!f->links || k.links == f->links))
-        return WCL_OK;
-    k = Workspace::EoKey{};
+    Workspace::FieldKey& k = ws->eo_key[prec == WCL_F64 ? 0 : 1];
+    Workspace::FieldKey held = k;
+    if (!f->links) held.buf[2] = 0;   // split links that this call does not use
+    if (held == key) return WCL_OK;
+    k = Workspace::FieldKey{};
     int hbad = 0;
     WCL_HIP(hipMemcpyAsync(bad, &hbad, sizeof(int), hipMemcpyHostToDevice, st));
     WCL_CHECK(launch_eo_fields(lat->g, prec, lat->clover[WCL_F64], lat->clover[prec], lat->gauge[prec], kappa, csw,
@@ -431,7 +428,7 @@ static int eo_fields(wcl_lattice* lat, Workspace* ws, double kappa, double csw, 
         wcl_set_error("the site term 1 + c_sw kappa C(x) is singular at some site (kappa %g, c_sw %g)", kappa, csw);
         return WCL_EINVAL;
     }
-    k = Workspace::EoKey{lat->uid, lat->clover_gen, kappa, csw, f->ainv, f->clov, f->links};
+    k = key;
     return WCL_OK;
 }
 

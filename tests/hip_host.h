@@ -18,6 +18,9 @@
 #include <utility>
 #include <vector>
 
+#define __align__(n) __attribute__((aligned(n)))
+#define HIP_SYMBOL(x) x
+
 namespace host {
 
 using Key = std::pair<hipStream_t, std::thread::id>;

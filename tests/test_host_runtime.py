@@ -28,3 +28,9 @@ def test_staged_transfers_are_ordered(tmp_path):
     out = run_driver(tmp_path, "stage_driver")
     for name in ("default-stream", "own-stream", "per-thread-stream"):
         assert f"ok {name}" in out
+
+
+def test_workspaces(tmp_path):
+    out = run_driver(tmp_path, "workspace_driver")
+    for name in ("rebuilt-after-failed-growth",):
+        assert f"ok {name}" in out
