@@ -827,6 +827,7 @@ static bool dslash_small(int V, int lps) { return lps == 1 && V <= 4096; }
 template <int GP, int SPI, int SPO, int EPI, int SPY>
 static int launch_t(const DslashArgs& a0, hipStream_t st) {
     DslashArgs a = a0;
+    a.lps = dslash_lanes(a0.lps);
     const bool xy = dslash_xy_layout(a.g);
     a.walk = tile_walk(a.g, xy ? 256 : 64, 1, a.nrhs, site_vec_bytes(SPI) + site_vec_bytes(SPO), site_field_bytes(GP),
                        xy);
@@ -867,6 +868,7 @@ static int launch_t(const DslashArgs& a0, hipStream_t st) {
 
 // workgroups (= dot-product partial sums) per rhs
 int dslash_partials_per_rhs(int V, int lps) {
+    lps = dslash_lanes(lps);
     const int spw = dslash_small(V, lps) ? 64 : 256 / lps;
     return (V + spw - 1) / spw;
 }

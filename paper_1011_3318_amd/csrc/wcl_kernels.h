@@ -113,6 +113,10 @@ inline TileWalk tile_walk(const Geom& g, int tile, int sites, int nrhs, size_t v
     return k;
 }
 
+// Lanes per site that a launch takes for a lattice's setting, which may come
+// from an autotuner's file: anything but 2 and 4 is 1.
+inline int dslash_lanes(int lps) { return lps == 2 || lps == 4 ? lps : 1; }
+
 // What a workgroup needs to find its tile stands together at the front: one
 // round of scalar loads before the first field load instead of two (12^4, one
 // rhs, FP32 6.6 -> 6.3 us, FP16 6.0 -> 5.8; 10x24x9x18, FP16, 2 rhs 9.6 -> 9.3).
@@ -120,7 +124,7 @@ struct DslashArgs {
     Geom g;
     TileWalk walk;       // set by launch_dslash
     int nrhs;
-    int lps;             // lanes per site: 1, 2 or 4
+    int lps;             // lanes per site (see dslash_lanes)
     const Scal* sc;      // optional: right-hand sides with sc[rhs].active == 0 are skipped
     const void* gauge;
     const void* clover;

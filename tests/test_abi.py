@@ -75,3 +75,17 @@ def test_no_dot_instruction_in_inline_asm():
             if m.group(1).strip():
                 bad.append((name, src.count("\n", 0, m.start()) + 1))
     assert not bad, bad
+
+
+def test_lanes_per_site_of_any_setting():
+    """A lattice's lanes per site may come from an autotuner's file: what is
+    not 2 or 4 counts as 1, in the number of workgroups too (a process of its
+    own, since a division by zero would end it)."""
+    import subprocess
+    import sys
+    code = ("import ctypes, torch; f = ctypes.CDLL(%r)._Z23dslash_partials_per_rhsii\n"
+            "for V in (4096, 5000):\n"
+            "    assert [f(V, k) for k in (0, 3, -1, 8, 1000)] == [f(V, 1)] * 5, V\n"
+            "    assert [f(V, 2), f(V, 4)] == [(V + 127) // 128, (V + 63) // 64]\n" % LIB)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])

@@ -1,5 +1,7 @@
 """GPU parity of the RAS domain operator, K_RAS and the solvers against the
 FP64 oracle, through the C ABI."""
+import re
+
 import numpy as np
 import pytest
 
@@ -310,4 +312,32 @@ def test_autotune_two_sources_and_arith(W, ctx):
         with pytest.raises(W.WclError) as e:
             W.autotune(lat, base, 0.125, 1.0, et, 1, nsrc=bad)
         assert e.value.code == W.EINVAL
+    lat.close()
+
+
+def test_autotune_cache_with_other_lanes(W, ctx, tmp_path):
+    """Lanes per site that no kernel has, read from a cache file, count as one
+    lane per site: D and its dot products are those of the default setting."""
+    dims = (16, 16, 4, 8)   # the exchange layout, whose launches have no spare lanes
+    U, lat = make(W, ctx, dims)
+    x = lat.pack(I.gaussian_source(dims, 2), W.F64)
+    base = W.SolverParams.make()
+    cache = str(tmp_path / "tune.jsonl")
+
+    def results():
+        out = [lat.unpack(lat.apply_D(p, 0.125, 1.0, lat.pack(I.gaussian_source(dims, 3), p), lat.empty(p)), p)
+               for p in (W.F64, W.F32, W.F16)]
+        phi = lat.zeros(W.F64)
+        lat.solve_bicgstab_f64(1e-10, 500, 0.11, 1.0, x, phi)
+        return out + [lat.unpack(phi, W.F64)]
+
+    want = results()
+    W.autotune(lat, base, 0.125, 1.0, x, cache_path=cache)
+    line = open(cache).read()
+    for lps in (0, 3, 1000, -2):
+        with open(cache, "w") as f:
+            f.write(re.sub(r'"lps": -?\d+', '"lps": %d' % lps, line))
+        W.autotune(lat, base, 0.125, 1.0, x, cache_path=cache)
+        for a, b in zip(results(), want):
+            assert np.array_equal(a, b), lps
     lat.close()
