@@ -180,10 +180,10 @@ typedef struct wcl_solve_stats {
 int wcl_init(int device, uint64_t hbm_budget_bytes, wcl_ctx** ctx);
 int wcl_finalize(wcl_ctx* ctx);
 const char* wcl_last_error(void);
-/* Bytes currently allocated by the library on the context's device.  One idle
- * staging block of at most 128 MiB, kept for the next transfer, is not counted:
- * it is freed as soon as another allocation needs the room, and by
- * wcl_finalize. */
+/* Bytes currently allocated by the library on the context's device.  Up to two
+ * idle staging blocks, together at most 128 MiB, kept for the next transfers, are
+ * not counted: they are freed as soon as another allocation needs the room, and
+ * by wcl_finalize. */
 uint64_t wcl_bytes_in_use(wcl_ctx* ctx);
 
 /* A lattice of dims = {Lx,Ly,Lz,Lt} (each >= 2) with fermion boundary phase

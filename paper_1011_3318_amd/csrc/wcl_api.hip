@@ -19,16 +19,18 @@ void wcl_set_error(const char* fmt, ...) {
     va_end(ap);
 }
 
-// Takes the idle staging block out of the context and frees it.
+// Takes the idle staging blocks out of the context and frees them.
 static void drop_idle(wcl_ctx* ctx) {
-    void* p;
+    void* p[2];
     {
         std::lock_guard<std::mutex> g(ctx->mu);
-        p = ctx->idle;
-        ctx->idle = nullptr;
-        ctx->idle_bytes = 0;
+        for (int k = 0; k < 2; ++k) {
+            p[k] = ctx->idle[k].p;
+            ctx->idle[k] = {};
+        }
     }
-    if (p) (void)hipFree(p);
+    for (void* q : p)
+        if (q) (void)hipFree(q);
 }
 
 int wcl_dev_alloc(wcl_ctx* ctx, void** p, size_t bytes) {
@@ -44,7 +46,7 @@ int wcl_dev_alloc(wcl_ctx* ctx, void** p, size_t bytes) {
             return WCL_ENOMEM;
         }
         ctx->in_use += bytes;
-        crowded = ctx->in_use + ctx->idle_bytes > ctx->budget;
+        crowded = ctx->in_use + ctx->idle[0].bytes + ctx->idle[1].bytes > ctx->budget;
     }
     if (crowded) drop_idle(ctx);
     hipError_t e = hipMalloc(p, bytes);
@@ -64,37 +66,40 @@ int wcl_dev_alloc(wcl_ctx* ctx, void** p, size_t bytes) {
     return WCL_OK;
 }
 
-int wcl_stage_alloc(wcl_ctx* ctx, void** p, size_t bytes, size_t* got) {
+int wcl_stage_alloc(wcl_ctx* ctx, void** p, size_t bytes) {
     {
         std::lock_guard<std::mutex> g(ctx->mu);
-        // only with room for what the call may allocate beside it (an upload's
-        // fields: 2.9 times its staging), which a block of just `bytes` would leave
-        if (ctx->idle && ctx->idle_bytes >= bytes && ctx->in_use + ctx->idle_bytes + 4 * bytes <= ctx->budget) {
-            *p = ctx->idle;
-            *got = ctx->idle_bytes;
-            ctx->in_use += ctx->idle_bytes;
-            ctx->idle = nullptr;
-            ctx->idle_bytes = 0;
-            return WCL_OK;
-        }
+        for (auto& b : ctx->idle)
+            if (b.p && b.bytes == bytes && ctx->in_use + bytes <= ctx->budget) {
+                *p = b.p;
+                b = {};
+                ctx->in_use += bytes;
+                return WCL_OK;
+            }
     }
-    *got = bytes;
     return wcl_dev_alloc(ctx, p, bytes);
 }
 
-void wcl_stage_free(wcl_ctx* ctx, void* p, size_t got) {
+void wcl_stage_free(wcl_ctx* ctx, void* p, size_t bytes) {
     if (!p) return;
-    void* old = p;
+    const size_t most = (size_t)128 << 20;   // the idle blocks together
+    void* gone[2] = {p, nullptr};
     {
         std::lock_guard<std::mutex> g(ctx->mu);
-        ctx->in_use -= got;
-        if (got <= (size_t)128 << 20 && got > ctx->idle_bytes && ctx->in_use + got <= ctx->budget) {
-            old = ctx->idle;
-            ctx->idle = p;
-            ctx->idle_bytes = got;
+        ctx->in_use -= bytes;
+        if (bytes <= most && ctx->in_use + bytes <= ctx->budget) {
+            auto &last = ctx->idle[0], &before = ctx->idle[1];
+            gone[0] = before.p;
+            before = last;
+            last = {p, bytes};
+            if (before.bytes + bytes > most || ctx->in_use + before.bytes + bytes > ctx->budget) {
+                gone[1] = before.p;
+                before = {};
+            }
         }
     }
-    if (old) (void)hipFree(old);
+    for (void* q : gone)
+        if (q) (void)hipFree(q);
 }
 
 uint64_t wcl_dev_room(wcl_ctx* ctx) {
@@ -162,7 +167,7 @@ int wcl_init(int device, uint64_t hbm_budget_bytes, wcl_ctx** out) {
 int wcl_finalize(wcl_ctx* ctx) {
     if (ctx) {
         stage_unref();
-        if (ctx->idle && hipSetDevice(ctx->device) == hipSuccess) drop_idle(ctx);
+        if ((ctx->idle[0].p || ctx->idle[1].p) && hipSetDevice(ctx->device) == hipSuccess) drop_idle(ctx);
     }
     delete ctx;
     return WCL_OK;
@@ -306,8 +311,7 @@ int wcl_upload_gauge(wcl_lattice* lat, const double* U) {
     int* flag_dev = nullptr;
     WCL_HIP(hipHostGetDevicePointer((void**)&flag_dev, lat->link_flag, 0));
     void* stage = nullptr;
-    size_t got = 0;
-    int rc = wcl_stage_alloc(lat->ctx, &stage, bytes, &got);
+    int rc = wcl_stage_alloc(lat->ctx, &stage, bytes);
     if (rc != WCL_OK) {
         // a field that is not SU(3) is reported as that also when nothing can
         // be staged; the allocation's own message stands otherwise
@@ -332,7 +336,7 @@ int wcl_upload_gauge(wcl_lattice* lat, const double* U) {
         wcl_set_error("wcl_upload_gauge: pack kernel failed");
         rc = WCL_EHIP;
     }
-    wcl_stage_free(lat->ctx, stage, got);
+    wcl_stage_free(lat->ctx, stage, bytes);
     if (rc == WCL_OK) {
         lat->has_gauge = true;
         lat->has_clover = false;
@@ -368,13 +372,12 @@ int wcl_upload_clover(wcl_lattice* lat, const double* C) {
     WCL_CHECK(ensure_fields(lat));
     const size_t bytes = (size_t)lat->V * 72 * sizeof(double);
     void* stage = nullptr;
-    size_t got = 0;
-    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes, &got));
+    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes));
     int rc = WCL_OK;
     rc = stage_to_device(lat->ctx->device, stage, C, bytes, 0);
     if (rc == WCL_OK) rc = launch_pack_clover(lat->g, (const double*)stage, lat->clover[0], lat->clover[1], lat->clover[2], 0);
     if (rc == WCL_OK && hipDeviceSynchronize() != hipSuccess) rc = WCL_EHIP;
-    wcl_stage_free(lat->ctx, stage, got);
+    wcl_stage_free(lat->ctx, stage, bytes);
     if (rc == WCL_EHIP) wcl_set_error("wcl_upload_clover: device copy or pack failed");
     if (rc == WCL_OK) {
         lat->has_clover = true;
@@ -392,11 +395,10 @@ int wcl_download_clover(wcl_lattice* lat, double* C) {
     WCL_CHECK(set_device(lat->ctx));
     const size_t bytes = (size_t)lat->V * 72 * sizeof(double);
     void* stage = nullptr;
-    size_t got = 0;
-    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes, &got));
+    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes));
     int rc = launch_unpack_clover(lat->g, lat->clover[0], (double*)stage, 0);
     if (rc == WCL_OK) rc = stage_to_host(lat->ctx->device, C, stage, bytes, 0);
-    wcl_stage_free(lat->ctx, stage, got);
+    wcl_stage_free(lat->ctx, stage, bytes);
     return rc;
 }
 
@@ -432,15 +434,14 @@ int wcl_pack_spinor(wcl_lattice* lat, int prec, int nrhs, const double* host_aos
     WCL_CHECK(set_device(lat->ctx));
     const size_t bytes = (size_t)lat->V * nrhs * 24 * sizeof(double);
     void* stage = nullptr;
-    size_t got = 0;
-    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes, &got));
+    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes));
     hipStream_t st = (hipStream_t)stream;
     int rc = WCL_OK;
     rc = stage_to_device(lat->ctx->device, stage, host_aos, bytes, st);
     if (rc == WCL_OK) rc = wcl_pack_spinor_dev(lat, prec, nrhs, (const double*)stage, dev_soa, stream);
     if (hipStreamSynchronize(st) != hipSuccess && rc == WCL_OK) rc = WCL_EHIP;
     if (rc == WCL_EHIP) wcl_set_error("wcl_pack_spinor: copy or pack failed");
-    wcl_stage_free(lat->ctx, stage, got);
+    wcl_stage_free(lat->ctx, stage, bytes);
     return rc;
 }
 
@@ -453,14 +454,13 @@ int wcl_unpack_spinor(wcl_lattice* lat, int prec, int nrhs, const void* dev_soa,
     WCL_CHECK(set_device(lat->ctx));
     const size_t bytes = (size_t)lat->V * nrhs * 24 * sizeof(double);
     void* stage = nullptr;
-    size_t got = 0;
-    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes, &got));
+    WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes));
     hipStream_t st = (hipStream_t)stream;
     int rc = wcl_unpack_spinor_dev(lat, prec, nrhs, dev_soa, (double*)stage, stream);
     if (rc == WCL_OK) rc = stage_to_host(lat->ctx->device, host_aos, stage, bytes, st);
     if (hipStreamSynchronize(st) != hipSuccess && rc == WCL_OK) rc = WCL_EHIP;
     if (rc == WCL_EHIP) wcl_set_error("wcl_unpack_spinor: unpack or copy failed");
-    wcl_stage_free(lat->ctx, stage, got);
+    wcl_stage_free(lat->ctx, stage, bytes);
     return rc;
 }
 

@@ -165,8 +165,10 @@ struct wcl_ctx {
     int num_cu;
     std::mutex mu;   // guards in_use (serving slots allocate concurrently)
     void* scratch = nullptr;   // this device's fixed scratch block (see static_scratch_setup)
-    void* idle = nullptr;      // staging block kept between calls (see wcl_stage_alloc), not part of in_use
-    size_t idle_bytes = 0;
+    struct Idle {
+        void* p = nullptr;
+        size_t bytes = 0;
+    } idle[2];   // staging blocks kept between calls, the last used first (see wcl_stage_alloc); not part of in_use
 };
 
 struct Workspace;  // solver scratch, defined in wcl_solver.hip
@@ -188,12 +190,14 @@ struct wcl_lattice {
 // device memory accounting against the context budget
 int wcl_dev_alloc(wcl_ctx* ctx, void** p, size_t bytes);
 uint64_t wcl_dev_room(wcl_ctx* ctx);   // what the budget still allows
-// A device block for the duration of a call that waits for its stream.  One
-// block of at most 128 MiB per context is kept for the next call (a hipMalloc
-// and a hipFree of 75 MB take 0.45 ms); it gives way to any other allocation
-// that needs its room.  *got receives the size to hand back.
-int wcl_stage_alloc(wcl_ctx* ctx, void** p, size_t bytes, size_t* got);
-void wcl_stage_free(wcl_ctx* ctx, void* p, size_t got);
+// A device block for the duration of a call that waits for its stream.  The
+// last two blocks of a context (links or clover and the spinors of one lattice),
+// together at most 128 MiB, are kept for the next call (a hipMalloc and a
+// hipFree of 75 MB take 0.45 ms).  They give way to any other allocation that
+// needs their room, and serve only a request of their own size, so that a call
+// is charged what it needs and a concurrent allocation is refused no earlier.
+int wcl_stage_alloc(wcl_ctx* ctx, void** p, size_t bytes);
+void wcl_stage_free(wcl_ctx* ctx, void* p, size_t bytes);
 void wcl_dev_free(wcl_ctx* ctx, void* p, size_t bytes);
 
 int check_prec(int prec);

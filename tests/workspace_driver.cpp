@@ -56,4 +56,46 @@ static int rebuilt_after_failed_growth() {
     return 0;
 }
 
-int main() { return rebuilt_after_failed_growth(); }
+// A transfer's staging is charged what the transfer needs, also when a larger
+// idle block is at hand: another thread's allocation that fits the budget
+// beside it is not refused.
+static int small_staging_beside_idle_block() {
+    const char* name = "small-staging-beside-idle-block";
+    const size_t M = (size_t)1 << 20;
+    Fixture fx(200 * M);
+    void *p = nullptr, *big = nullptr, *other = nullptr;
+    HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &big, 75 * M) == WCL_OK);   // a large upload leaves its block
+    wcl_stage_free(&fx.ctx, big, 75 * M);
+    HOST_CHECK(name, fx.ctx.in_use == 0);
+    HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &p, 2 * M) == WCL_OK);      // a small one
+    HOST_CHECK(name, wcl_dev_alloc(&fx.ctx, &other, 190 * M) == WCL_OK);  // meanwhile
+    wcl_dev_free(&fx.ctx, other, 190 * M);
+    wcl_stage_free(&fx.ctx, p, 2 * M);
+    HOST_CHECK(name, fx.ctx.in_use == 0 && host::blocks.size() == 1);     // the 75 MiB gave way
+    // two sizes in turn: each block serves its own size again
+    HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &big, 75 * M) == WCL_OK);
+    wcl_stage_free(&fx.ctx, big, 75 * M);
+    for (int k = 0; k < 4; ++k) {
+        void* q = nullptr;
+        const size_t n = k % 2 ? 75 * M : 2 * M;
+        HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &q, n) == WCL_OK && q == (k % 2 ? big : p));
+        HOST_CHECK(name, fx.ctx.in_use == n);
+        wcl_stage_free(&fx.ctx, q, n);
+    }
+    // never more than two, nor more than 128 MiB
+    for (size_t n : {3 * M, 4 * M, 100 * M, 60 * M, 129 * M}) {
+        HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &p, n) == WCL_OK);
+        wcl_stage_free(&fx.ctx, p, n);
+        size_t sum = 0;
+        for (auto& kv : host::blocks) sum += kv.second;
+        HOST_CHECK(name, host::blocks.size() <= 2 && sum <= 128 * M && fx.ctx.in_use == 0);
+    }
+    // they give way when idle, and an allocation past the budget is refused
+    HOST_CHECK(name, wcl_dev_alloc(&fx.ctx, &other, 200 * M) == WCL_OK && host::blocks.size() == 1);
+    HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &p, M) == WCL_ENOMEM);
+    wcl_dev_free(&fx.ctx, other, 200 * M);
+    std::printf("ok %s\n", name);
+    return 0;
+}
+
+int main() { return rebuilt_after_failed_growth() || small_staging_beside_idle_block(); }
