@@ -80,14 +80,14 @@ int wcl_stage_alloc(wcl_ctx* ctx, void** p, size_t bytes) {
     return wcl_dev_alloc(ctx, p, bytes);
 }
 
-void wcl_stage_free(wcl_ctx* ctx, void* p, size_t bytes) {
+void wcl_stage_free(wcl_ctx* ctx, void* p, size_t bytes, bool idle) {
     if (!p) return;
     const size_t most = (size_t)128 << 20;   // the idle blocks together
     void* gone[2] = {p, nullptr};
     {
         std::lock_guard<std::mutex> g(ctx->mu);
         ctx->in_use -= bytes;
-        if (bytes <= most && ctx->in_use + bytes <= ctx->budget) {
+        if (idle && bytes <= most && ctx->in_use + bytes <= ctx->budget) {
             auto &last = ctx->idle[0], &before = ctx->idle[1];
             gone[0] = before.p;
             before = last;
@@ -336,7 +336,7 @@ int wcl_upload_gauge(wcl_lattice* lat, const double* U) {
         wcl_set_error("wcl_upload_gauge: pack kernel failed");
         rc = WCL_EHIP;
     }
-    wcl_stage_free(lat->ctx, stage, bytes);
+    wcl_stage_free(lat->ctx, stage, bytes, rc == WCL_OK);
     if (rc == WCL_OK) {
         lat->has_gauge = true;
         lat->has_clover = false;
@@ -377,7 +377,7 @@ int wcl_upload_clover(wcl_lattice* lat, const double* C) {
     rc = stage_to_device(lat->ctx->device, stage, C, bytes, 0);
     if (rc == WCL_OK) rc = launch_pack_clover(lat->g, (const double*)stage, lat->clover[0], lat->clover[1], lat->clover[2], 0);
     if (rc == WCL_OK && hipDeviceSynchronize() != hipSuccess) rc = WCL_EHIP;
-    wcl_stage_free(lat->ctx, stage, bytes);
+    wcl_stage_free(lat->ctx, stage, bytes, rc == WCL_OK);
     if (rc == WCL_EHIP) wcl_set_error("wcl_upload_clover: device copy or pack failed");
     if (rc == WCL_OK) {
         lat->has_clover = true;
@@ -398,7 +398,7 @@ int wcl_download_clover(wcl_lattice* lat, double* C) {
     WCL_CHECK(wcl_stage_alloc(lat->ctx, &stage, bytes));
     int rc = launch_unpack_clover(lat->g, lat->clover[0], (double*)stage, 0);
     if (rc == WCL_OK) rc = stage_to_host(lat->ctx->device, C, stage, bytes, 0);
-    wcl_stage_free(lat->ctx, stage, bytes);
+    wcl_stage_free(lat->ctx, stage, bytes, rc == WCL_OK);
     return rc;
 }
 
@@ -441,7 +441,7 @@ int wcl_pack_spinor(wcl_lattice* lat, int prec, int nrhs, const double* host_aos
     if (rc == WCL_OK) rc = wcl_pack_spinor_dev(lat, prec, nrhs, (const double*)stage, dev_soa, stream);
     if (hipStreamSynchronize(st) != hipSuccess && rc == WCL_OK) rc = WCL_EHIP;
     if (rc == WCL_EHIP) wcl_set_error("wcl_pack_spinor: copy or pack failed");
-    wcl_stage_free(lat->ctx, stage, bytes);
+    wcl_stage_free(lat->ctx, stage, bytes, rc == WCL_OK);
     return rc;
 }
 
@@ -460,7 +460,7 @@ int wcl_unpack_spinor(wcl_lattice* lat, int prec, int nrhs, const void* dev_soa,
     if (rc == WCL_OK) rc = stage_to_host(lat->ctx->device, host_aos, stage, bytes, st);
     if (hipStreamSynchronize(st) != hipSuccess && rc == WCL_OK) rc = WCL_EHIP;
     if (rc == WCL_EHIP) wcl_set_error("wcl_unpack_spinor: unpack or copy failed");
-    wcl_stage_free(lat->ctx, stage, bytes);
+    wcl_stage_free(lat->ctx, stage, bytes, rc == WCL_OK);
     return rc;
 }
 

@@ -196,8 +196,10 @@ uint64_t wcl_dev_room(wcl_ctx* ctx);   // what the budget still allows
 // hipFree of 75 MB take 0.45 ms).  They give way to any other allocation that
 // needs their room, and serve only a request of their own size, so that a call
 // is charged what it needs and a concurrent allocation is refused no earlier.
+// idle: nothing queued uses the block any more, it may be kept; else (a call that
+// failed) it is freed, which waits for the device.
 int wcl_stage_alloc(wcl_ctx* ctx, void** p, size_t bytes);
-void wcl_stage_free(wcl_ctx* ctx, void* p, size_t bytes);
+void wcl_stage_free(wcl_ctx* ctx, void* p, size_t bytes, bool idle);
 void wcl_dev_free(wcl_ctx* ctx, void* p, size_t bytes);
 
 int check_prec(int prec);

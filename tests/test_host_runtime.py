@@ -32,5 +32,5 @@ def test_staged_transfers_are_ordered(tmp_path):
 
 def test_workspaces(tmp_path):
     out = run_driver(tmp_path, "workspace_driver")
-    for name in ("rebuilt-after-failed-growth", "small-staging-beside-idle-block"):
+    for name in ("rebuilt-after-failed-growth", "small-staging-beside-idle-block", "failed-call-leaves-no-work"):
         assert f"ok {name}" in out

@@ -4,6 +4,7 @@
 
 #include "wcl_api.hip"
 #include "wcl_solver.hip"
+#include "wcl_stage.cpp"
 
 static int n_eo = 0, n_inv = 0;
 int launch_eo_fields(const Geom&, int, const void*, const void*, const void*, double, double, void*, void*, void*,
@@ -65,27 +66,27 @@ static int small_staging_beside_idle_block() {
     Fixture fx(200 * M);
     void *p = nullptr, *big = nullptr, *other = nullptr;
     HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &big, 75 * M) == WCL_OK);   // a large upload leaves its block
-    wcl_stage_free(&fx.ctx, big, 75 * M);
+    wcl_stage_free(&fx.ctx, big, 75 * M, true);
     HOST_CHECK(name, fx.ctx.in_use == 0);
     HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &p, 2 * M) == WCL_OK);      // a small one
     HOST_CHECK(name, wcl_dev_alloc(&fx.ctx, &other, 190 * M) == WCL_OK);  // meanwhile
     wcl_dev_free(&fx.ctx, other, 190 * M);
-    wcl_stage_free(&fx.ctx, p, 2 * M);
+    wcl_stage_free(&fx.ctx, p, 2 * M, true);
     HOST_CHECK(name, fx.ctx.in_use == 0 && host::blocks.size() == 1);     // the 75 MiB gave way
     // two sizes in turn: each block serves its own size again
     HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &big, 75 * M) == WCL_OK);
-    wcl_stage_free(&fx.ctx, big, 75 * M);
+    wcl_stage_free(&fx.ctx, big, 75 * M, true);
     for (int k = 0; k < 4; ++k) {
         void* q = nullptr;
         const size_t n = k % 2 ? 75 * M : 2 * M;
         HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &q, n) == WCL_OK && q == (k % 2 ? big : p));
         HOST_CHECK(name, fx.ctx.in_use == n);
-        wcl_stage_free(&fx.ctx, q, n);
+        wcl_stage_free(&fx.ctx, q, n, true);
     }
     // never more than two, nor more than 128 MiB
     for (size_t n : {3 * M, 4 * M, 100 * M, 60 * M, 129 * M}) {
         HOST_CHECK(name, wcl_stage_alloc(&fx.ctx, &p, n) == WCL_OK);
-        wcl_stage_free(&fx.ctx, p, n);
+        wcl_stage_free(&fx.ctx, p, n, true);
         size_t sum = 0;
         for (auto& kv : host::blocks) sum += kv.second;
         HOST_CHECK(name, host::blocks.size() <= 2 && sum <= 128 * M && fx.ctx.in_use == 0);
@@ -98,4 +99,30 @@ static int small_staging_beside_idle_block() {
     return 0;
 }
 
-int main() { return rebuilt_after_failed_growth() || small_staging_beside_idle_block(); }
+// A call that fails hands its staging block back only when nothing queued can
+// still use it: the next call may take the block at once, on another stream.
+static bool fail_pack = false;
+int launch_pack_clover(const Geom&, const double*, void*, void*, void*, hipStream_t) {
+    return fail_pack ? WCL_EHIP : WCL_OK;
+}
+static int failed_call_leaves_no_work() {
+    const char* name = "failed-call-leaves-no-work";
+    Fixture fx;
+    wcl_lattice* lat = fx.lattice(4);
+    lat->has_gauge = true;
+    void* pinned = nullptr;   // a pinned source is copied asynchronously
+    const size_t n = (size_t)lat->V * 72;
+    hipHostMalloc(&pinned, n * sizeof(double), 0);
+    std::memset(pinned, 0, n * sizeof(double));
+    fail_pack = true;
+    HOST_CHECK(name, wcl_upload_clover(lat, (const double*)pinned) == WCL_EHIP);
+    for (auto& kv : host::queues) HOST_CHECK(name, kv.second.done == kv.second.work.size());
+    fail_pack = false;
+    HOST_CHECK(name, wcl_upload_clover(lat, (const double*)pinned) == WCL_OK);
+    std::printf("ok %s\n", name);
+    return 0;
+}
+
+int main() {
+    return rebuilt_after_failed_growth() || small_staging_beside_idle_block() || failed_call_leaves_no_work();
+}
