@@ -16,8 +16,9 @@ struct Scal {
 
 // ------------------------------------------------- host transfers ------
 // Copies between host memory of the caller (pageable or not) and the device,
-// ordered on st (wcl_stage.cpp).  stage_to_device: the source may be changed on
-// return; stage_to_host: the destination is complete on return.
+// ordered on st (wcl_stage.cpp).  stage_to_device: the source is read until st
+// has been waited for (a pinned one is copied in place); stage_to_host: the
+// destination is complete on return.
 int stage_to_device(int device, void* dev, const void* host, size_t bytes, hipStream_t st);
 int stage_to_host(int device, void* host, const void* dev, size_t bytes, hipStream_t st);
 void stage_ref();     // one per context: the staging memory is freed with the last

@@ -239,6 +239,9 @@ struct wcl_server {
             if (rc2 == WCL_OK && hipStreamSynchronize(s->st) != hipSuccess) rc2 = WCL_EHIP;
             if (rc2 != WCL_OK) rc = rc2;
         }
+        // a pinned source or solution may still be in a queued copy; the caller
+        // may free it once the result is out
+        if (rc != WCL_OK && rc != WCL_ENOTCONV) (void)hipStreamSynchronize(s->st);
         const double t_done = now_s();
         std::lock_guard<std::mutex> g(mu);
         for (int k = 0; k < n; ++k) {

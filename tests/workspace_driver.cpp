@@ -5,6 +5,7 @@
 #include "wcl_api.hip"
 #include "wcl_solver.hip"
 #include "wcl_stage.cpp"
+#include "wcl_server.cpp"
 
 static int n_eo = 0, n_inv = 0;
 int launch_eo_fields(const Geom&, int, const void*, const void*, const void*, double, double, void*, void*, void*,
@@ -123,6 +124,37 @@ static int failed_call_leaves_no_work() {
     return 0;
 }
 
+// A request that fails is reported only when nothing queued reads its source
+// any more: the caller may free it then.
+int launch_pack_spinor(const Geom&, int, int, const double*, void*, size_t, hipStream_t) {
+    return fail_pack ? WCL_EHIP : WCL_OK;
+}
+static int failed_request_releases_source() {
+    const char* name = "failed-request-releases-source";
+    Fixture fx;
+    int handle = 0;
+    wcl_server srv;
+    srv.ctx = &fx.ctx;
+    wcl_server::Slot slot;
+    slot.st = (hipStream_t)&handle;
+    slot.ws = wcl_workspace_new(&fx.ctx);
+    Job j;
+    j.lat = fx.lattice(4);
+    void* pinned = nullptr;
+    hipHostMalloc(&pinned, (size_t)j.lat->V * 24 * sizeof(double), 0);
+    j.req.eta_host = j.req.phi_host = (double*)pinned;
+    slot.jobs.push_back(j);
+    fail_pack = true;
+    srv.run_job(&slot);
+    fail_pack = false;
+    HOST_CHECK(name, srv.done.size() == 1 && srv.done.begin()->second.status == WCL_EHIP);
+    host::Queue& q = host::queue(slot.st);
+    HOST_CHECK(name, !q.work.empty() && q.done == q.work.size());
+    wcl_workspace_delete(slot.ws);
+    std::printf("ok %s\n", name);
+    return 0;
+}
+
 int main() {
-    return rebuilt_after_failed_growth() || small_staging_beside_idle_block() || failed_call_leaves_no_work();
+    return failed_request_releases_source() || rebuilt_after_failed_growth() || small_staging_beside_idle_block() || failed_call_leaves_no_work();
 }
