@@ -298,6 +298,7 @@ int launch_blk_unpack(const BlockArgs& a, const float* ws, double* out, hipStrea
 struct Workspace;
 Workspace* wcl_workspace_new(wcl_ctx* ctx);
 void wcl_workspace_delete(Workspace* w);
+void workspace_begin(Workspace* w);   // a new call: buffers it does not ask for may be given up
 size_t workspace_bytes(const Workspace* w);
 void workspace_get(Workspace* w, const char* name, size_t bytes, void** out, int* rc);
 // Nested RAS-BiCGStab on an explicit workspace and stream (Sec. 3).

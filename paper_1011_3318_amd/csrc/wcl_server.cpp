@@ -216,6 +216,7 @@ struct wcl_server {
         const int64_t V = j.lat->V;
         const size_t b64 = spinor_rhs_bytes(WCL_F64, V), stage_b = (size_t)V * 24 * sizeof(double);
         void *eta = nullptr, *phi = nullptr, *stage = nullptr;
+        workspace_begin(s->ws);
         workspace_get(s->ws, "srv.eta", b64 * n, &eta, &rc);
         if (rc == WCL_OK) workspace_get(s->ws, "srv.phi", b64 * n, &phi, &rc);
         if (rc == WCL_OK) workspace_get(s->ws, "srv.stage", stage_b, &stage, &rc);

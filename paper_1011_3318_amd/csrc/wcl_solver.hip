@@ -93,8 +93,10 @@ struct Workspace {
         void* p;
         size_t bytes;
         uint64_t id;      // number of the allocation, never used again
+        uint64_t call;    // the call that asked for it last
     };
     uint64_t last_id = 0;
+    uint64_t call = 0;    // counted by the entry points that use the workspace
     std::vector<Item> items;
     struct Pinned {
         std::string name;
@@ -103,17 +105,35 @@ struct Workspace {
     };
     std::vector<Pinned> pinned;   // host mirrors of the scalar arrays, one per solver level
 
+    void drop(Item& it) {
+        wcl_dev_free(ctx, it.p, it.bytes);
+        it.p = nullptr;
+        it.bytes = 0;
+    }
+    // Frees the fields kept from earlier calls that this call has not asked for
+    // (the site-term inverse, what the even-odd reduction holds): they can be
+    // built again.  The pointers a call holds are those it has asked for.
+    bool drop_kept_fields() {
+        bool any = false;
+        for (auto& it : items)
+            if (it.p && it.call != call && (it.name.rfind("ainv.", 0) == 0 || it.name.rfind("eo.", 0) == 0)) {
+                drop(it);
+                any = true;
+            }
+        return any;
+    }
     // id (optional): the number of the buffer's allocation
     int get(const std::string& name, size_t bytes, void** out, uint64_t* id = nullptr) {
         size_t k = 0;
         while (k < items.size() && items[k].name != name) ++k;
-        if (k == items.size()) items.push_back(Item{name, nullptr, 0, 0});
+        if (k == items.size()) items.push_back(Item{name, nullptr, 0, 0, 0});
         Item& it = items[k];
+        it.call = call;
         if (it.bytes < bytes) {
-            wcl_dev_free(ctx, it.p, it.bytes);
-            it.p = nullptr;
-            it.bytes = 0;
-            WCL_CHECK(wcl_dev_alloc(ctx, &it.p, bytes));
+            drop(it);
+            int rc = wcl_dev_alloc(ctx, &it.p, bytes);
+            if (rc == WCL_ENOMEM && drop_kept_fields()) rc = wcl_dev_alloc(ctx, &it.p, bytes);
+            WCL_CHECK(rc);
             it.bytes = bytes;
             it.id = ++last_id;
         }
@@ -159,6 +179,7 @@ Workspace* wcl_workspace_new(wcl_ctx* ctx) {
     return w;
 }
 void wcl_workspace_delete(Workspace* w) { delete w; }
+void workspace_begin(Workspace* w) { ++w->call; }
 
 size_t workspace_bytes(const Workspace* w) {
     size_t b = 0;
@@ -196,8 +217,10 @@ void wcl_free_workspace(wcl_lattice* lat) {
     lat->ws = nullptr;
 }
 
+// the lattice's own workspace, once per call of an entry point
 static Workspace* lattice_ws(wcl_lattice* lat) {
     if (!lat->ws) lat->ws = wcl_workspace_new(lat->ctx);
+    workspace_begin(lat->ws);
     return lat->ws;
 }
 

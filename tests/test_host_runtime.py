@@ -32,6 +32,6 @@ def test_staged_transfers_are_ordered(tmp_path):
 
 def test_workspaces(tmp_path):
     out = run_driver(tmp_path, "workspace_driver")
-    for name in ("rebuilt-after-failed-growth", "small-staging-beside-idle-block", "failed-call-leaves-no-work",
+    for name in ("kept-fields-give-way", "rebuilt-after-failed-growth", "small-staging-beside-idle-block", "failed-call-leaves-no-work",
                  "failed-request-releases-source"):
         assert f"ok {name}" in out

@@ -58,6 +58,41 @@ static int rebuilt_after_failed_growth() {
     return 0;
 }
 
+// The even-odd fields and the site-term inverse of the Jacobi domain solver are
+// kept from call to call, but a budget that holds either is enough for both in
+// turn, and kept split links do not take the room of another call's fields.
+static int kept_fields_give_way() {
+    const char* name = "kept-fields-give-way";
+    const int64_t V = 8 * 8 * 8 * 8;
+    const size_t inverse = clover_bytes(WCL_F64, V) + clover_bytes(WCL_F32, V) + clover_bytes(WCL_F16, V);
+    Fixture fx(inverse + 256);
+    wcl_lattice* lat = fx.lattice(8);
+    void* inv[3];
+    EoFields f64, f32;
+    for (int k = 0; k < 2; ++k) {
+        HOST_CHECK(name, site_inverse(lat, lattice_ws(lat), 0.1, 1.0, nullptr, inv) == WCL_OK);
+        Workspace* ws = lattice_ws(lat);
+        HOST_CHECK(name, eo_fields(lat, ws, 0.1, 1.0, WCL_F64, false, nullptr, &f64) == WCL_OK);
+        HOST_CHECK(name, eo_fields(lat, ws, 0.1, 1.0, WCL_F32, true, nullptr, &f32) == WCL_OK);
+        HOST_CHECK(name, host::blocks.count(f64.ainv) && host::blocks.count(f64.clov));   // this call's own stay
+    }
+    // with room for split links they are made; a later call gets their room
+    fx.ctx.budget = inverse + 256 + 2 * gauge_bytes(WCL_F64, V / 2) + 16 * spinor_rhs_bytes(WCL_F64, V);
+    EoFields g;
+    HOST_CHECK(name, eo_fields(lat, lattice_ws(lat), 0.1, 1.0, WCL_F64, true, nullptr, &g) == WCL_OK && g.links);
+    void* v = nullptr;
+    const size_t rest = fx.ctx.budget - clover_bytes(WCL_F64, V) - 256;   // all but A^{-1} and C of this call
+    Workspace* ws = lattice_ws(lat);
+    HOST_CHECK(name, eo_fields(lat, ws, 0.1, 1.0, WCL_F64, false, nullptr, &f64) == WCL_OK);
+    HOST_CHECK(name, ws->get("vectors", rest, &v) == WCL_OK);
+    HOST_CHECK(name, ws->get("more", 256, &v) == WCL_ENOMEM);
+    HOST_CHECK(name, host::blocks.count(f64.ainv) && host::blocks.count(f64.clov));
+    wcl_free_workspace(lat);
+    HOST_CHECK(name, fx.ctx.in_use == 0);
+    std::printf("ok %s\n", name);
+    return 0;
+}
+
 // A transfer's staging is charged what the transfer needs, also when a larger
 // idle block is at hand: another thread's allocation that fits the budget
 // beside it is not refused.
@@ -156,5 +191,5 @@ static int failed_request_releases_source() {
 }
 
 int main() {
-    return failed_request_releases_source() || rebuilt_after_failed_growth() || small_staging_beside_idle_block() || failed_call_leaves_no_work();
+    return kept_fields_give_way() || failed_request_releases_source() || rebuilt_after_failed_growth() || small_staging_beside_idle_block() || failed_call_leaves_no_work();
 }
