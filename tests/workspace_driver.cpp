@@ -35,6 +35,7 @@ struct Fixture {
 static int rebuilt_after_failed_growth() {
     const char* name = "rebuilt-after-failed-growth";
     Fixture fx;
+    n_eo = n_inv = 0;
     Workspace* ws = wcl_workspace_new(&fx.ctx);
     wcl_lattice *a = fx.lattice(4), *b = fx.lattice(8);
     EoFields f, f2;
