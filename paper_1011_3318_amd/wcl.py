@@ -118,10 +118,14 @@ def check(rc: int, what: str = ""):
 def _stream(stream):
     if stream is None:
         # the handle behind torch.cuda.current_stream(), without the Stream
-        # object (2.9 us of a 7.1 us D-apply call at 8^4)
+        # object (2.9 us of a 7.1 us D-apply call at 8^4) where this torch has
+        # the two calls, which are not part of its public interface
         if not torch.cuda.is_initialized():
             torch.cuda.init()
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
