@@ -1342,7 +1342,9 @@ WCL_DEV void crossing_hops(const BlockArgs& a, const FF& F, int rhs, int gi, con
 // folded into the links, and the clover is loaded only after the residual
 // update: 162-167 VGPRs, no spill (193 before).  First / later sweep of 4 steps
 // at 32^4: 195 / 248 -> 172 / 209 us; NRAS 5: 1183 -> 1021 us.  RES == 1 (overlap)
-// needs the clover during its residual update and keeps two.
+// needs the clover during its residual update and keeps two, and with them the
+// whole solution in registers (197 and 233 VGPRs): 16^4, 2^4 domains grown by one
+// site per side, 3 sweeps of 4 steps 634 us with 16 components in LDS, 613 without.
 //
 // FEW: a grid that cannot fill the third place (at most two domains per CU)
 // keeps the whole solution in registers (191-197 VGPRs) and spares each step
@@ -1352,7 +1354,7 @@ WCL_DEV void crossing_hops(const BlockArgs& a, const FF& F, int rhs, int gi, con
 // The operations and their order are the same, so the bits are.
 template <bool DOT, int RES, bool FEW>
 struct FusedShape {
-    static constexpr int xl = DOT && !FEW ? 16 : 0;   // components of the solution kept in LDS
+    static constexpr int xl = DOT && !FEW && RES != 1 ? 16 : 0;   // components of the solution kept in LDS
     static constexpr int lds_words = DOT ? 36 + xl : 72;
     static constexpr int min_waves = DOT && RES != 1 && !FEW ? 3 : WCL_FUSED_MINWAVES;
     // with registers to spare the clover's loads start with the others
