@@ -89,6 +89,13 @@ __host__ __device__ inline int walk_rhs(const TileWalk& k, int lb, int n, int nr
 // Measured, D-apply, whole ranges and groups / this rule: 32^4 FP32 131 / 126 us
 // (two planes: 150), FP64 285 / 278, 3 rhs FP32 298 / 282, FP64 631 / 590;
 // 16^3x32 with 12 rhs FP32 125 / 110 (groups of 4: 114, of 2: 129), FP64 263 / 247.
+// Columns are walked side by side only where an XCD's eighth of the launch is
+// more than 1.25 t slices of a z range (Lt * nCz / 8): in less, nearly every t
+// neighbour belongs to another XCD, while storage order has whole columns in
+// one.  Storage order / side by side, 3 rhs: 48x24x8x5 FP32 17.4 / 18.5 us, FP64
+// 35.0 / 37.5; 20x28x16x4 12.7 / 13.5 and 24.8 / 25.8; 32x21x4x10 10.8 / 11.2 and
+// 21.4 / 22.8; but 28x28x8x12 24.8 / 23.6 and 63.0 / 60.5, 48x6x8x16 12.9 / 12.0
+// and 25.6 / 24.5, 24^3x6 25.3 / 24.8 and 66.3 / 62.1.
 // by_nrhs = false keeps the walk of the tiles the same for every nrhs, for
 // launches whose workgroups sum over several tiles.
 inline TileWalk tile_walk(const Geom& g, int tile, int sites, int nrhs, size_t vec, size_t fields, bool by_nrhs) {
@@ -105,6 +112,7 @@ inline TileWalk tile_walk(const Geom& g, int tile, int sites, int nrhs, size_t v
     const size_t per_tile = (size_t)tile * k.nxy * ((by_nrhs ? k.group : 1) * vec + fields);
     while (k.zt % 2 == 0 && k.zt * per_tile > (3u << 20) && k.zt / 2 * s >= 4 * g.c[0] * g.c[1]) k.zt /= 2;
     if (k.nxy == 1 && k.zt == k.tiles) k.tiles = 0;   // that is storage order
+    if (k.nxy > 1 && g.L[3] * g.nC[2] <= 10) k.tiles = 0;
     const int nsub = k.tiles / k.zt, widest = std::max(std::max(k.tiles, k.nxy), k.Lt);
     if ((uint64_t)(g.V / s) * widest >> 32) k.tiles = 0;   // past the range of walk_div
     k.m_zt = walk_magic(k.zt);

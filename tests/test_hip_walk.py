@@ -117,3 +117,11 @@ def test_schur_without_room_for_split_links(W, dims):
             ctx.close()
         assert used[prec, 1] < used[prec, 0]
         assert np.array_equal(got[prec, 0], got[prec, 1])
+
+
+# t extents that let cut columns be walked side by side (more than 10 t slices
+# of all z ranges), just past the rule and beside it: 24x8x8 has one z range,
+# 12x20x16 two
+@pytest.mark.parametrize("dims", [(24, 8, 8, 10), (24, 8, 8, 12), (12, 12, 4, 14), (12, 20, 16, 6)])
+def test_walk_side_by_side(W, dims):
+    test_walk_matches_oracle(W, dims)
