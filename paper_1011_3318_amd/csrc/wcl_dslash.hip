@@ -493,7 +493,10 @@ __global__ __launch_bounds__(256, WCL_XY_MINWAVES) void k_dslash_xy16(DslashArgs
 // 64 sites, all their loads in flight at once, and the four partial sums meet
 // in LDS, where each wavefront finishes a quarter of the components.  For
 // launches that leave most SIMDs idle, where the time is one wavefront's chain
-// of loads and arithmetic: this has a quarter of that chain.
+// of loads and arithmetic: this has a quarter of that chain.  Larger batches are
+// bound by what their loads fetch past the L2, so each XCD takes consecutive
+// tiles of a group of at most six right-hand sides, as the other launches do
+// (rhs innermost over all XCDs: 8^4 with 12 rhs FP64 14.1 us, so 11.4).
 // A quarter of a spinor: components 3 w .. 3 w + 2 (6 reals), by storage.
 template <int P>
 struct SpinorQuarter;
@@ -611,7 +614,8 @@ __global__ __launch_bounds__(256, GP == WCL_F64 ? 2 : 4) void k_dslash_w4(Dslash
     __shared__ T part[4][24][64];
     __shared__ float smax[4][64];
     const int tiles = gridDim.x / a.nrhs;
-    const int rhs = blockIdx.x % a.nrhs, tile = blockIdx.x / a.nrhs;
+    int tile;
+    const int rhs = walk_rhs(a.walk, xcd_remap(blockIdx.x, gridDim.x), tiles, a.nrhs, &tile);
     if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
     const int i = tile * 64 + l, V = a.g.V;
@@ -670,6 +674,75 @@ __global__ __launch_bounds__(256, GP == WCL_F64 ? 2 : 4) void k_dslash_w4(Dslash
         }
         block_reduce3(d, a.partial + 3 * ((size_t)tile + (size_t)rhs * tiles));
     }
+}
+
+// The same sums, bit for bit, by one wavefront per 64 sites through the hop
+// pipeline, for FP16 launches of more workgroups than the chip holds at once:
+// there the exchange through LDS costs more than the shorter chain gains.
+// Hops K..7: acc collects direction K / 2 (c0, c1: block 0 and block 1 of the
+// site term, the first summands of x and y), v and t the sums of directions.
+template <int K, int D>
+WCL_DEV void sum_chain16(const DslashArgs& a, const char* in, const int nbr[8], const int lnk[8], const float ph[8],
+                         float mk, float z, h2v sb[D][12], float ss[D], h2v ub[D][9], const float c0[12],
+                         const float c1[12], float acc[24], float t[24], float v[24]) {
+    if constexpr (K < 8) {
+        constexpr int slot = K % D;
+        if constexpr (K % 2 == 0)
+#pragma unroll
+            for (int k = 0; k < 24; ++k)
+                acc[k] = K == 0 && k < 12 ? c0[k % 12] : K == 2 && k >= 12 ? c1[k % 12] : 0.f;
+        hop_compute16<K / 2, (K % 2) == 0>(sb[slot], ub[slot], mk * ph[K] * ss[slot], z, acc);
+        if constexpr (K + D < 8) {
+            ss[slot] = load_spinor16(in, a.g.V, nbr[K + D], sb[slot]);
+            load_link16<false>(a.gauge, a.g.V, (K + D) / 2, lnk[K + D], z, ub[slot]);
+        }
+        if constexpr (K % 2 == 1)
+#pragma unroll
+            for (int k = 0; k < 24; ++k) {
+                if (K == 1) v[k] = acc[k];
+                if (K == 3) v[k] = v[k] + acc[k];
+                if (K == 5) t[k] = acc[k];
+                if (K == 7) v[k] = v[k] + (t[k] + acc[k]);
+            }
+        sum_chain16<K + 1, D>(a, in, nbr, lnk, ph, mk, z, sb, ss, ub, c0, c1, acc, t, v);
+    }
+}
+
+__global__ __launch_bounds__(256, 3) void k_dslash_sum16(DslashArgs a) {
+    constexpr int D = WCL_PIPE_DEPTH;
+    int pos;
+    const int rhs = walk_rhs(a.walk, xcd_remap(blockIdx.x, gridDim.x), gridDim.x / a.nrhs, a.nrhs, &pos);
+    if (a.sc && !a.sc[rhs].active) return;   // uniform over the workgroup
+    const int i = pos * 256 + threadIdx.x, V = a.g.V;
+    if (i >= V) return;
+    const char* in = (const char*)a.in + rhs * a.in_stride;
+    int x[4], nbr[8], lnk[8];
+    float ph[8];
+    geom_coords(a.g, i, x);
+    hop_sites(a.g, i, x, nbr, lnk, ph);
+    float z = 0.f;   // opaque zero: the first product of every chain stays a v_dot2
+    asm volatile("" : "+v"(z));
+    h2v sb[D][12], ub[D][9];
+    float ss[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        ss[k] = load_spinor16(in, V, nbr[k], sb[k]);
+        load_link16<false>(a.gauge, V, k / 2, lnk[k], z, ub[k]);
+    }
+    float c0[12], c1[12], acc[24], t[24], v[24];
+    {
+        h2v s[12];
+        const float sc = load_spinor16(in, V, i, s);
+        float c[24];
+        clover_site16<false>(a.clover, V, i, s, sc, (float)(a.csw * a.kappa), z, c);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            c0[k] = c[k];
+            c1[k] = c[12 + k];
+        }
+    }
+    sum_chain16<0, D>(a, in, nbr, lnk, ph, (float)(-a.kappa), z, sb, ss, ub, c0, c1, acc, t, v);
+    SpinorIO<WCL_F16>::store((char*)a.out + rhs * a.out_stride, V, i, v);
 }
 
 // ------------------------------------------------ several lanes per site
@@ -821,7 +894,12 @@ static size_t dslash_launch_bytes(int V, int gp, int spi, int spo) {
 // Past that the fourfold wavefronts no longer find idle SIMDs (12^4 with 4 rhs
 // FP32 12.0 / 13.4 us per call, 12 rhs 22 / 28; 12x12x18x20 FP32 9.7 / 11.9).
 // The rule looks at the volume only: a batched right-hand side gets the bits
-// of its own single launch.
+// of its own single launch.  Batches at 8^4, per call, one lane per site / this:
+// 12 rhs FP32 8.2 / 6.6 us, FP64 12.4 / 11.4, FP16 7.1 / 5.7; 48 rhs FP32
+// 18.5 / 17.0, FP64 37.5 / 34.0.
+// FP16 with more than 1400 tiles in all goes through k_dslash_sum16: 18 rhs (1152
+// tiles) 7.7 us here, 8.4 there; 24 rhs (1536) 8.8 / 8.6, 48 rhs 14.5 / 11.7.
+constexpr int kSumTiles = 1400;
 static bool dslash_small(int V, int lps) { return lps == 1 && V <= 4096; }
 
 template <int GP, int SPI, int SPO, int EPI, int SPY>
@@ -834,7 +912,13 @@ static int launch_t(const DslashArgs& a0, hipStream_t st) {
     if constexpr (EPI != DS_AXPY || SPO != WCL_F16)
         if (dslash_small(a.g.V, a.lps)) {
             const int n = (a.g.V + 63) / 64 * a.nrhs;
-            k_dslash_w4<GP, SPI, SPO, EPI, SPY><<<n, 256, 0, st>>>(a);
+            bool done = false;
+            if constexpr (GP == WCL_F16 && SPI == WCL_F16 && SPO == WCL_F16 && EPI == DS_PLAIN)
+                if (n > kSumTiles) {
+                    k_dslash_sum16<<<(a.g.V + 255) / 256 * a.nrhs, 256, 0, st>>>(a);
+                    done = true;
+                }
+            if (!done) k_dslash_w4<GP, SPI, SPO, EPI, SPY><<<n, 256, 0, st>>>(a);
             WCL_HIP(hipGetLastError());
             return WCL_OK;
         }

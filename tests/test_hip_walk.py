@@ -125,3 +125,26 @@ def test_schur_without_room_for_split_links(W, dims):
 @pytest.mark.parametrize("dims", [(24, 8, 8, 10), (24, 8, 8, 12), (12, 12, 4, 14), (12, 20, 16, 6)])
 def test_walk_side_by_side(W, dims):
     test_walk_matches_oracle(W, dims)
+
+
+# batches on small lattices: groups of right-hand sides (7 = 4 + 3, 13 = 5 + 5 + 3)
+# and, in FP16, the last count of tiles below the pipelined form's and the first above
+# (1400): 2x5x13x2 has 5 tiles, the last of 4 sites
+@pytest.mark.parametrize("dims,nrhs", [((8, 8, 8, 8), 7), ((8, 8, 8, 8), 13), ((8, 8, 8, 8), 21), ((8, 8, 8, 8), 22),
+                                       ((2, 5, 13, 2), 280), ((2, 5, 13, 2), 281), ((15, 13, 7, 3), 22)])
+def test_small_batches(W, dims, nrhs):
+    ctx = W.Context(0)
+    U = I.random_gauge(dims, 0.5, 1)
+    lat = W.Lattice(ctx, dims, BC)
+    lat.upload_gauge(U)
+    o = Oracle(dims, U, bc=BC)
+    psi = I.gaussian_source(dims, 4, nrhs=nrhs)
+    for prec, tol in ((W.F64, 1e-13), (W.F32, 1e-5), (W.F16, 2e-3)):
+        many = lat.unpack(lat.apply_D(prec, 0.126, 1.3, lat.pack(psi, prec, nrhs), lat.empty(prec, nrhs), nrhs=nrhs),
+                          prec, nrhs)
+        assert rel_err(many[nrhs - 1], o.apply_D(psi[nrhs - 1], 0.126, 1.3)) <= tol
+        for k in range(nrhs) if nrhs < 30 else (0, 3, 4, 5, 6, nrhs // 2, nrhs - 1):
+            one = lat.apply_D(prec, 0.126, 1.3, lat.pack(psi[k], prec), lat.empty(prec))
+            assert np.array_equal(lat.unpack(one, prec), many[k]), (prec, k)
+    lat.close()
+    ctx.close()
