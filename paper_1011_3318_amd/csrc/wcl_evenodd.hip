@@ -192,14 +192,16 @@ static int launch_eo_n(const EoArgs& a0, hipStream_t st) {
     // Non-temporal field loads only for one rhs streaming more than the 256 MB
     // Infinity Cache holds.  A launch reads each split link once, the next
     // launch (the other parity) reads it again: links that take no more than
-    // half of that cache stay in it.  apply_schur, cached / non-temporal
-    // links: FP32 24^3x48 (127 MB) 156 / 164 us, FP64 (255 MB) 363 / 341,
-    // FP32 32^4 (201 MB) 239 / 223.
+    // half of that cache stay in it for a solve, which applies one operator over
+    // and over.  Cached / non-temporal links, FP32 24^3x48 (127 MB): solve 14.5 /
+    // 15.1 ms, apply_schur with changing fields 162 / 164 us; apply_schur of one
+    // field again and again, FP64 24^3x48 (255 MB) 363 / 341 us, FP32 32^4
+    // (201 MB) 239 / 223.
     const size_t links = 2 * gauge_bytes(P, a.Vh);
     const bool nt = a.nrhs == 1 && links + clover_bytes(P, a.Vh) + 2 * spinor_rhs_bytes(P, a.Vh) > (256u << 20);
     if (!nt) k_eo<P, MODE, EPI, SL, FULL, false, false><<<grid, 256, 0, st>>>(a);
-    else if (links <= (128u << 20)) k_eo<P, MODE, EPI, SL, FULL, true, false><<<grid, 256, 0, st>>>(a);
-    else k_eo<P, MODE, EPI, SL, FULL, true, true><<<grid, 256, 0, st>>>(a);
+    else if (SL && links > (128u << 20)) k_eo<P, MODE, EPI, SL, FULL, true, SL><<<grid, 256, 0, st>>>(a);
+    else k_eo<P, MODE, EPI, SL, FULL, true, false><<<grid, 256, 0, st>>>(a);
     WCL_HIP(hipGetLastError());
     return WCL_OK;
 }
@@ -209,35 +211,33 @@ static int launch_eo_t(const EoArgs& a, hipStream_t st) {
     return a.links ? launch_eo_n<P, MODE, EPI, true, FULL>(a, st) : launch_eo_n<P, MODE, EPI, false, FULL>(a, st);
 }
 
+// The forms that are called: the operator between full-lattice fields
+// (wcl_apply_schur) at both precisions, a solve's FP32 level with its dot
+// products, and its FP64 level, which reads full-lattice links only.
 int launch_eo(const EoArgs& a, int prec, int mode, int epi, hipStream_t st) {
     if (a.g.V % 2 || a.Vh * 2 != a.g.V) {
         wcl_set_error("even-odd: half volume %d does not match the lattice", a.Vh);
         return WCL_EINVAL;
     }
-#define WCL_EO(P)                                                                                      \
-    if (prec == P) {                                                                                   \
-        switch (mode) {                                                                                \
-            case EO_INV:                                                                               \
-                return a.full ? launch_eo_t<P, EO_INV, DS_PLAIN, true>(a, st)                          \
-                              : launch_eo_t<P, EO_INV, DS_PLAIN, false>(a, st);                        \
-            case EO_SCHUR:                                                                             \
-                return a.full           ? launch_eo_t<P, EO_SCHUR, DS_PLAIN, true>(a, st)              \
-                       : epi == DS_DOT  ? launch_eo_t<P, EO_SCHUR, DS_DOT, false>(a, st)               \
-                       : epi == DS_AXPY ? launch_eo_t<P, EO_SCHUR, DS_AXPY, false>(a, st)              \
-                                        : launch_eo_t<P, EO_SCHUR, DS_PLAIN, false>(a, st);            \
-            default: break;                                                                            \
-        }                                                                                              \
+    if (a.full && epi == DS_PLAIN) {
+        if (prec == WCL_F64 && mode == EO_INV) return launch_eo_t<WCL_F64, EO_INV, DS_PLAIN, true>(a, st);
+        if (prec == WCL_F64 && mode == EO_SCHUR) return launch_eo_t<WCL_F64, EO_SCHUR, DS_PLAIN, true>(a, st);
+        if (prec == WCL_F32 && mode == EO_INV) return launch_eo_t<WCL_F32, EO_INV, DS_PLAIN, true>(a, st);
+        if (prec == WCL_F32 && mode == EO_SCHUR) return launch_eo_t<WCL_F32, EO_SCHUR, DS_PLAIN, true>(a, st);
+    } else if (!a.full && prec == WCL_F32) {
+        if (mode == EO_INV && epi == DS_PLAIN) return launch_eo_t<WCL_F32, EO_INV, DS_PLAIN, false>(a, st);
+        if (mode == EO_SCHUR && epi == DS_DOT) return launch_eo_t<WCL_F32, EO_SCHUR, DS_DOT, false>(a, st);
+    } else if (!a.full && prec == WCL_F64 && !a.links) {
+        if (epi == DS_PLAIN) switch (mode) {
+                case EO_INV: return launch_eo_n<WCL_F64, EO_INV, DS_PLAIN, false, false>(a, st);
+                case EO_PREP: return launch_eo_n<WCL_F64, EO_PREP, DS_PLAIN, false, false>(a, st);
+                case EO_RECON: return launch_eo_n<WCL_F64, EO_RECON, DS_PLAIN, false, false>(a, st);
+                case EO_SITEINV: return launch_eo_n<WCL_F64, EO_SITEINV, DS_PLAIN, false, false>(a, st);
+                default: break;
+            }
+        if (mode == EO_SCHUR && epi == DS_DOT) return launch_eo_n<WCL_F64, EO_SCHUR, DS_DOT, false, false>(a, st);
+        if (mode == EO_SCHUR && epi == DS_AXPY) return launch_eo_n<WCL_F64, EO_SCHUR, DS_AXPY, false, false>(a, st);
     }
-    WCL_EO(WCL_F64)
-    WCL_EO(WCL_F32)
-#undef WCL_EO
-    // the reduction's own steps are FP64 and run once per solve
-    if (prec == WCL_F64) switch (mode) {
-            case EO_PREP: return launch_eo_t<WCL_F64, EO_PREP, DS_PLAIN, false>(a, st);
-            case EO_RECON: return launch_eo_t<WCL_F64, EO_RECON, DS_PLAIN, false>(a, st);
-            case EO_SITEINV: return launch_eo_t<WCL_F64, EO_SITEINV, DS_PLAIN, false>(a, st);
-            default: break;
-        }
-    wcl_set_error("even-odd: unsupported precision %d or mode %d", prec, mode);
+    wcl_set_error("even-odd: no launch of precision %d, mode %d, epilogue %d", prec, mode, epi);
     return WCL_EINVAL;
 }
