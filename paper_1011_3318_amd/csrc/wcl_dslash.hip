@@ -21,7 +21,9 @@
 // hop of their site and the backward hop of the next one, and use cached loads
 // always: non-temporal ones cost 24^3x48 245 (FP64), 113 (FP32) and 44 us
 // (FP16) against 207, 92 and 43, and 32^4 296, 139 and 72 against 287, 131
-// and 65.
+// and 65.  These launches were repeated on one configuration; with others in
+// between, where nothing stays in a cache, 32^4 FP16 takes 71.8 us, 72.2 with
+// non-temporal links.
 template <bool NT, int GP, int SPI, typename T>
 WCL_DEV void clover_site(const DslashArgs& a, const char* in, int i, T acc[24]) {
     const int V = a.g.V;
